@@ -88,6 +88,7 @@ struct holo_plan {
   // reversed): class 0's angles in ascending order, then class 1's
   std::vector<int> adj_order;
   int adj_n0 = 0;
+  int c_split = 1;                          // slots of the probe-gradient sums
   // workspace layout (byte offsets)
   size_t off_Q = 0, off_G = 0, off_P = 0, off_ub = 0, off_uTb = 0, off_psi = 0, off_X = 0, off_S = 0,
          off_F = 0, ws_bytes = 0, n_fpart = 0, off_psi2 = 0;
@@ -238,7 +239,8 @@ static void layout_workspace(holo_plan* P) {
   const size_t fr = (size_t)P->H * P->W * sizeof(float2);
   size_t o = 0;
   P->off_Q = o;   o = align_up(o + fr * P->nd);
-  P->off_G = o;   o = align_up(o + fr * P->nd);
+  P->c_split = pass_c_split(P->H, P->W, P->nd, P->chunk);
+  P->off_G = o;   o = align_up(o + fr * P->nd * P->c_split);
   P->off_P = o;   o = align_up(o + fr);
   // z-blocked copies of the volume read by the ray sums (one per walk
   // direction), rows padded by kFwdPad zero columns on each side
@@ -682,13 +684,6 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     }
     HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_rows_prop(g, rj, st); }));
     HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_cols_prop(g, cj, Fpart, st); }));
-    if (with_ref && want_gq) {
-      PropJobs r2{}, c2{};
-      r2.job[r2.n++] = PropJob{Pref, Pref, nullptr, chirp_ref(nd), 1, 0};
-      c2.job[c2.n++] = PropJob{Pref, Pref, nullptr, chirp_ref(nd), 1, 0};
-      HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_rows_prop(g, r2, st); }));
-      HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_cols_prop(g, c2, Fpart, st); }));
-    }
   }
   // Fourier-slice projector: psi of every angle of the call into the
   // sinogram buffer now, slab by slab; the chunks copy theirs from there
@@ -720,8 +715,6 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
       return launch_block_volume(g, u, ub, xwalk ? uTb : nullptr, st);
     }));
   }
-  if (want_gq) HOLO_HIP(timed(P, HOLO_K_OTHER, st, [&] { return launch_fill_zero(Gacc, nd * HW, st); }));
-
   const bool frames_back = want_gq || want_gu;
   const int2* d_groups = (const int2*)((const char*)P->d_tables + P->off_groups);
   // Chunks [c0, c1): whole ray-sum groups (clipped to [k0, k1)), at most
@@ -784,6 +777,7 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
   for (size_t ci = 0; ci < chunks.size(); ++ci) {
     const int c0 = chunks[ci].x, c1 = chunks[ci].y;
     const int Kc = c1 - c0;
+    const int first = ci == 0 ? 1 : 0;
     float2* const psi_c = psib[ci & 1];
     if (fs) {
       HOLO_HIP(timed(P, HOLO_K_OTHER, st, [&] {
@@ -827,11 +821,12 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
         const PadJob ra = pj(X, X, hw, nf, chirp_det(0), nd, 1, 0, nullptr, 0);
         HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] { return launch_rows_pad(g, ra, st); }));
         HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-          return launch_frames_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, c0, Kc, st);
+          return launch_frames_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, first, P->c_split, c0,
+                                 Kc, st);
         }));
         if (want_gq && Pbuf)
           HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-            return launch_probe_shift_acc(g, Gacc, Pbuf, c0, Kc, st);
+            return launch_probe_shift_acc(g, Gacc, Pbuf, first, P->c_split, c0, Kc, st);
           }));
         if (want_gu)
           HOLO_HIP(timed(P, HOLO_K_PASS_D, st, [&] {
@@ -869,11 +864,12 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     }
     if ((mode == kGrad || mode == kAdj) && frames_back) {
       HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-        return launch_pass_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, c0, Kc, st);
+        return launch_pass_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, first, P->c_split, c0, Kc,
+                             st);
       }));
       if (want_gq && Pbuf)
         HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-          return launch_probe_shift_acc(g, Gacc, Pbuf, c0, Kc, st);
+          return launch_probe_shift_acc(g, Gacc, Pbuf, first, P->c_split, c0, Kc, st);
         }));
       if (want_gu)
         HOLO_HIP(timed(P, HOLO_K_PASS_D, st, [&] {
@@ -902,24 +898,29 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     }));
   }
   if (want_gq) {
+    if (P->c_split > 1)
+      HOLO_HIP(timed(P, HOLO_K_OTHER, st, [&] {
+        return launch_sum_slots(Gacc, P->c_split, nd * HW, st);
+      }));
     if (padded) {
       const int cp = chirp_probe(nd, 0);
       const PadJob rg = pj(Gacc, Gacc, hw, nd, cp, nd, 1, 0, nullptr, 0);
       const PadJob cg = pj(Gacc, Gacc, hw, nd, cp, nd, 1, 0, nullptr, 0);
       HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_rows_pad(g, rg, st); }));
       HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_cols_pad(g, cg, Fpart, st); }));
+      HOLO_HIP(timed(P, HOLO_K_OTHER, st, [&] {
+        return launch_sum_frames(Gacc, nd, with_ref ? Pref : nullptr, gq, HW, st);
+      }));
     } else {
-      PropJobs rj{}, cj{};
-      for (int j = 0; j < nd; ++j) {
+      // rows of every G_j and of the reference residual, then one column pass
+      // over all of them
+      PropJobs rj{};
+      for (int j = 0; j < nd; ++j)
         rj.job[rj.n++] = PropJob{Gacc + j * HW, Gacc + j * HW, nullptr, chirp_probe(nd, j), 1, 0};
-        cj.job[cj.n++] = PropJob{Gacc + j * HW, Gacc + j * HW, nullptr, chirp_probe(nd, j), 1, 0};
-      }
+      if (with_ref) rj.job[rj.n++] = PropJob{Pref, Pref, nullptr, chirp_ref(nd), 1, 0};
       HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_rows_prop(g, rj, st); }));
-      HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_cols_prop(g, cj, Fpart, st); }));
+      HOLO_HIP(timed(P, HOLO_K_PROBE, st, [&] { return launch_cols_gq(g, rj, gq, st); }));
     }
-    HOLO_HIP(timed(P, HOLO_K_OTHER, st, [&] {
-      return launch_sum_frames(Gacc, nd, with_ref ? Pref : nullptr, gq, HW, st);
-    }));
   }
   if (want_F) {
     // the first ref_tiles slots hold the reference term's cost

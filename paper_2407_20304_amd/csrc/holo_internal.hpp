@@ -167,16 +167,24 @@ hipError_t launch_copy_rows(const float2* src, size_t src_pitch, float2* dst, si
 hipError_t launch_frames_x(const DevGeom& g, const float2* psi, const float2* Q, float2* X,
                            int k_first, int Kc, hipStream_t st);
 hipError_t launch_frames_c(const DevGeom& g, float2* X, const float2* psi, const float2* Q,
-                           float2* G, float2* Pbuf, int accumulate, int k_first, int Kc,
-                           hipStream_t st);
+                           float2* G, float2* Pbuf, int accumulate, int first, int split,
+                           int k_first, int Kc, hipStream_t st);
 hipError_t launch_pass_b(const DevGeom& g, int mode, const float2* src, float2* X,
                          const float* amp, double* Fpart, int Kc, hipStream_t st);
 hipError_t launch_pass_c(const DevGeom& g, float2* X, const float2* psi, const float2* Q,
-                         float2* G, float2* Pbuf, int accumulate, int k_first, int Kc,
-                         hipStream_t st);
+                         float2* G, float2* Pbuf, int accumulate, int first, int split,
+                         int k_first, int Kc, hipStream_t st);
 // G_j += sum_k S_{-s_kj}(Pbuf[k][j]) for the Kc angles of a chunk (probe shifts).
-hipError_t launch_probe_shift_acc(const DevGeom& g, float2* G, const float2* Pbuf, int k_first,
-                                  int Kc, hipStream_t st);
+hipError_t launch_probe_shift_acc(const DevGeom& g, float2* G, const float2* Pbuf, int first,
+                                  int split, int k_first, int Kc, hipStream_t st);
+// The chunk's angles are shared by `split` workgroups per row block in the
+// three launches above; each adds its angles into a slot of its own,
+// G[slot][j] (set instead of added to in the first chunk).
+constexpr int kPassCGroups = 1024, kPassCMaxSplit = 32;
+int pass_c_split(int H, int W, int nd, int chunk);
+hipError_t launch_sum_slots(float2* G, int ns, size_t n, hipStream_t st);
+// g_q = sum over the jobs of the conjugate column propagation of their frames.
+hipError_t launch_cols_gq(const DevGeom& g, const PropJobs& jobs, float2* gq, hipStream_t st);
 hipError_t launch_pass_d(const DevGeom& g, const float2* X, const float2* psi, float2* S,
                          int k_first, int Kc, hipStream_t st);
 hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uTb, float2* psi,

@@ -209,13 +209,16 @@ __global__ __launch_bounds__(kThreads) void k_pass_a(const float2* __restrict__ 
   for (int e = 0; e < E; ++e) out[lt + e * TL] = v[e];
 }
 
+// (four waves per SIMD where the plan's stages are even: without the bound
+// the 1024-point instantiation takes 129 VGPRs)
 template <int W, bool PS>   // PS: probe shifts set
-__global__ __launch_bounds__(kThreads) void k_pass_c(float2* __restrict__ X,
+__global__ __launch_bounds__(kThreads, !PS && W % 3 != 0 ? 4 : 1) void k_pass_c(float2* __restrict__ X,
                                                      const float2* __restrict__ psi,
                                                      const float2* __restrict__ Q,
                                                      float2* __restrict__ G,
                                                      float2* __restrict__ Pbuf, DevGeom g,
-                                                     int accumulate, int k_first, int Kc) {
+                                                     int accumulate, int first, int k_first,
+                                                     int Kc) {
   constexpr int TL = rows_tl(W), LPW = rows_lpw(W), E = W / TL;
   __shared__ float2 s_tw[fft_line_len(W)];
   __shared__ float2 s_line[LPW][fft_line_len(W)];
@@ -223,6 +226,9 @@ __global__ __launch_bounds__(kThreads) void k_pass_c(float2* __restrict__ X,
   const int lp = fpi(lt);   // padded position of the thread's first element
   const int z = blockIdx.x * LPW + line;
   const int j = blockIdx.y;
+  // this workgroup's share of the chunk's angles, and its slot of G
+  const int per = (Kc + gridDim.z - 1) / gridDim.z;
+  const int kb = blockIdx.z * per, ke = min(kb + per, Kc);
   for (int i = threadIdx.x; i < W; i += kThreads) s_tw[fpi(i)] = g.twW[i];
   const double m = g.mag[j];
   const float2* Qrow = Q + ((size_t)j * g.H + z) * W;
@@ -233,7 +239,7 @@ __global__ __launch_bounds__(kThreads) void k_pass_c(float2* __restrict__ X,
   for (int e = 0; e < E; ++e) gacc[e] = make_float2(0.f, 0.f);
   if constexpr (wave_lines(TL)) __syncthreads();   // s_tw
 
-  for (int k = 0; k < Kc; ++k) {
+  for (int k = kb; k < ke; ++k) {
     float2* row = X + (((size_t)k * g.nd + j) * g.H + z) * W;
 #pragma unroll
     for (int e = 0; e < E; ++e) L[rowpos<TL>(lp, lt, e)] = row[lt + e * TL];
@@ -273,11 +279,11 @@ __global__ __launch_bounds__(kThreads) void k_pass_c(float2* __restrict__ X,
     }
   }
   if (accumulate && !PS) {
-    float2* grow = G + ((size_t)j * g.H + z) * W;
+    float2* grow = G + (((size_t)blockIdx.z * g.nd + j) * g.H + z) * W;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int s = lt + e * TL;
-      float2 v = grow[s];
+      const float2 v = first ? make_float2(0.f, 0.f) : grow[s];
       grow[s] = make_float2(v.x + gacc[e].x, v.y + gacc[e].y);
     }
   }
@@ -500,6 +506,55 @@ __global__ __launch_bounds__(kColThreads) void k_cols_prop(PropJobs jobs, double
   }
 }
 
+// Columns of the probe gradient: g_q = sum_i D_{-rho_i} f_i over the jobs'
+// frames (the G_j of every plane and the reference residual, rows already
+// propagated).  A column tile's spectra are weighted by the conjugate
+// transfer factors and summed in registers, so one inverse transform serves
+// every frame.  Tiles of 4 columns: latency-bound, so the grid (W / 4
+// workgroups) should reach as many CUs as it can.
+constexpr int kGqTC = 4;
+template <int H>
+__global__ __launch_bounds__(kThreads) void k_cols_gq(PropJobs jobs, float2* __restrict__ gq,
+                                                      DevGeom g) {
+  constexpr int TC = kGqTC, TLc = kThreads / TC, EC = H / TLc;
+  static_assert(TLc == 64 && H % TLc == 0, "one wavefront per column");
+  __shared__ float2 s_tw[fft_line_len(H)];
+  __shared__ float2 s_col[TC][col_pitch(H)];
+  const int c = threadIdx.x / TLc, lt = threadIdx.x % TLc;
+  const int W = g.W;
+  const int s0 = blockIdx.x * TC;
+  for (int i = threadIdx.x; i < H; i += kThreads) s_tw[fpi(i)] = g.twH[i];
+  float2* Lc = s_col[c];
+  float2 acc[EC];
+#pragma unroll
+  for (int e = 0; e < EC; ++e) acc[e] = make_float2(0.f, 0.f);
+  for (int n = 0; n < jobs.n; ++n) {
+    const float2* in = jobs.job[n].src + s0;
+    __syncthreads();                   // the previous frame's tile has been read
+    for (int i = threadIdx.x; i < H * TC; i += kThreads) {
+      const int zz = i / TC, cc = i % TC;
+      s_col[cc][fpi(zz)] = in[(size_t)zz * W + cc];
+    }
+    __syncthreads();                   // tile and s_tw
+    float2 v[EC];
+#pragma unroll
+    for (int e = 0; e < EC; ++e) v[e] = Lc[fpi(lt + e * TLc)];
+    fft_e<H, TLc, false, true, true>(v, Lc, s_tw, lt);
+    const float2* ch = g.chirpH + (size_t)jobs.job[n].chirp * H;
+#pragma unroll
+    for (int e = 0; e < EC; ++e) acc[e] = cadd(acc[e], cmulc(v[e], ch[lt + e * TLc]));
+  }
+  fft_e<H, TLc, true, true, true>(acc, Lc, s_tw, lt);
+  __syncthreads();                     // every column's exchange reads are done
+#pragma unroll
+  for (int e = 0; e < EC; ++e) Lc[fpi(lt + e * TLc)] = acc[e];
+  __syncthreads();
+  for (int i = threadIdx.x; i < H * TC; i += kThreads) {
+    const int zz = i / TC, cc = i % TC;
+    gq[(size_t)zz * W + s0 + cc] = s_col[cc][fpi(zz)];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Padded propagation: a line of n samples is set in the centre of a line of
 // 2n (zeros outside), transformed there with the 2n-point transfer row, and
@@ -637,16 +692,20 @@ __global__ __launch_bounds__(kThreads) void k_frames_c(float2* __restrict__ X,
                                                        const float2* __restrict__ Q,
                                                        float2* __restrict__ G,
                                                        float2* __restrict__ Pbuf, DevGeom g,
-                                                       int accumulate, int k_first, int Kc) {
+                                                       int accumulate, int first, int k_first,
+                                                       int Kc) {
   const size_t HW = (size_t)g.H * g.W;
   const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= HW * g.nd) return;
+  // this workgroup's share of the chunk's angles, and its slot of G
+  const int per = (Kc + gridDim.y - 1) / gridDim.y;
+  const int kb = blockIdx.y * per, ke = min(kb + per, Kc);
   const int j = (int)(i / HW);
   const int p = (int)(i % HW);
   const int z = p / g.W, s = p % g.W;
   const double m = g.mag[j];
   float2 gacc = make_float2(0.f, 0.f);
-  for (int k = 0; k < Kc; ++k) {
+  for (int k = kb; k < ke; ++k) {
     float2* xp = X + ((size_t)k * g.nd + j) * HW + p;
     const float2 w = *xp;
     double ty, tx;
@@ -672,8 +731,9 @@ __global__ __launch_bounds__(kThreads) void k_frames_c(float2* __restrict__ X,
     *xp = cmulc(w, qv);
   }
   if (accumulate && !g.pshift) {
-    const float2 v = G[i];
-    G[i] = make_float2(v.x + gacc.x, v.y + gacc.y);
+    float2* gp = G + (size_t)blockIdx.y * g.nd * HW + i;
+    const float2 v = first ? make_float2(0.f, 0.f) : *gp;
+    *gp = make_float2(v.x + gacc.x, v.y + gacc.y);
   }
 }
 
@@ -797,6 +857,22 @@ __global__ void k_sum_frames(const float2* __restrict__ G, int nd, const float2*
   }
 }
 
+// out[i] = sum over s < ns of G[s n + i], in place over slot 0.
+__global__ void k_sum_slots(float2* __restrict__ G, int ns, size_t n) {
+  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  for (; i < n; i += stride) {
+    float2 acc = G[i];
+#pragma unroll 8
+    for (int s = 1; s < ns; ++s) {
+      const float2 v = G[(size_t)s * n + i];
+      acc.x += v.x;
+      acc.y += v.y;
+    }
+    G[i] = acc;
+  }
+}
+
 // Deterministic single-workgroup sum of double partials.
 // Workgroup b sums parts[b per, min(n, (b + 1) per)) into out[b]; a fixed
 // partition and order, so the total is reproducible bit for bit.
@@ -888,6 +964,17 @@ hipError_t launch_cols_prop(const DevGeom& g, const PropJobs& jobs, double* Fpar
   return hipGetLastError();
 }
 
+hipError_t launch_cols_gq(const DevGeom& g, const PropJobs& jobs, float2* gq, hipStream_t st) {
+  const unsigned grid = g.W / kGqTC;
+  switch (g.H) {
+#define CASE(N) case N: k_cols_gq<N><<<grid, kThreads, 0, st>>>(jobs, gq, g); break;
+    HOLO_FOR_SIZES(CASE)
+#undef CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 #define HOLO_FOR_PAD_SIZES(X) X(64) X(128) X(192) X(256) X(384) X(512) X(1024)
 
 hipError_t launch_rows_pad(const DevGeom& g, const PadJob& jb, hipStream_t st) {
@@ -945,11 +1032,11 @@ hipError_t launch_frames_x(const DevGeom& g, const float2* psi, const float2* Q,
 }
 
 hipError_t launch_frames_c(const DevGeom& g, float2* X, const float2* psi, const float2* Q,
-                           float2* G, float2* Pbuf, int accumulate, int k_first, int Kc,
-                           hipStream_t st) {
+                           float2* G, float2* Pbuf, int accumulate, int first, int split,
+                           int k_first, int Kc, hipStream_t st) {
   const size_t n = (size_t)g.H * g.W * g.nd;
-  k_frames_c<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, st>>>(
-      X, psi, Q, G, Pbuf, g, accumulate, k_first, Kc);
+  const dim3 grid((unsigned)((n + kThreads - 1) / kThreads), split);
+  k_frames_c<<<grid, kThreads, 0, st>>>(X, psi, Q, G, Pbuf, g, accumulate, first, k_first, Kc);
   return hipGetLastError();
 }
 
@@ -1010,19 +1097,34 @@ hipError_t launch_pass_b(const DevGeom& g, int mode, const float2* src, float2* 
   return hipGetLastError();
 }
 
+// Workgroups that share a chunk's angles in pass C (and in the elementwise
+// form of a padded plan and the probe-shift sums).  With one workgroup per
+// block of rows and plane, each walking every angle of the chunk one after
+// the other, few CUs work below 1024 px; so the angles are shared out until
+// kPassCGroups workgroups run, each adding into its own slot of G, which
+// k_sum_slots adds up.  Per chunk, one workgroup against the shares: 64 px
+// 381 -> 19 us (90 angles), 128 px 315 -> 26, 256 px 342 -> 88, 512 px
+// 428 -> 293 us (64 angles).  More shares cost slot traffic (256 px: 88 us
+// with 1024 workgroups in all, 96 with 2048, 112 with 4096), and 1024-px
+// rows (2048 workgroups) gain nothing from them.
+int pass_c_split(int H, int W, int nd, int chunk) {
+  const int rows = H / rows_per_wg(W) * nd;
+  return std::max(1, std::min({(kPassCGroups + rows - 1) / rows, chunk, kPassCMaxSplit}));
+}
+
 hipError_t launch_pass_c(const DevGeom& g, float2* X, const float2* psi, const float2* Q,
-                         float2* G, float2* Pbuf, int accumulate, int k_first, int Kc,
-                         hipStream_t st) {
-  const dim3 grid(g.H / rows_per_wg(g.W), g.nd);
+                         float2* G, float2* Pbuf, int accumulate, int first, int split,
+                         int k_first, int Kc, hipStream_t st) {
+  const dim3 grid(g.H / rows_per_wg(g.W), g.nd, split);
   switch (g.W) {
 #define CASE(N)                                                                            \
   case N:                                                                                  \
     if (g.pshift)                                                                          \
       k_pass_c<N, true><<<grid, kThreads, 0, st>>>(X, psi, Q, G, Pbuf, g, accumulate,       \
-                                                   k_first, Kc);                            \
+                                                   first, k_first, Kc);                     \
     else                                                                                   \
       k_pass_c<N, false><<<grid, kThreads, 0, st>>>(X, psi, Q, G, nullptr, g, accumulate,   \
-                                                    k_first, Kc);                           \
+                                                    first, k_first, Kc);                    \
     break;
     HOLO_FOR_SIZES(CASE)
 #undef CASE
@@ -1042,29 +1144,34 @@ hipError_t launch_pass_d(const DevGeom& g, const float2* X, const float2* psi, f
 // (y + s_y, x + s_x): the transposed probe shift S_{-s_kj}.
 __global__ __launch_bounds__(kThreads) void k_probe_shift_acc(float2* __restrict__ G,
                                                               const float2* __restrict__ Pbuf,
-                                                              DevGeom g, int k_first, int Kc) {
+                                                              DevGeom g, int first, int k_first,
+                                                              int Kc) {
   const size_t HW = (size_t)g.H * g.W;
   const int j = blockIdx.y;
+  // this workgroup's share of the chunk's angles, and its slot of G
+  const int per = (Kc + gridDim.z - 1) / gridDim.z;
+  const int kb = blockIdx.z * per, ke = min(kb + per, Kc);
+  float2* Gj = G + ((size_t)blockIdx.z * g.nd + j) * HW;
   for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < HW;
        i += (size_t)gridDim.x * kThreads) {
     const int y = (int)(i / g.W), x = (int)(i % g.W);
-    float2 acc = G[(size_t)j * HW + i];
-    for (int k = 0; k < Kc; ++k) {
+    float2 acc = first ? make_float2(0.f, 0.f) : Gj[i];
+    for (int k = kb; k < ke; ++k) {
       const float* ps = g.pshift + ((size_t)(k_first + k) * g.nd + j) * 2;
       const float2 v = sample_circ(Pbuf + ((size_t)k * g.nd + j) * HW, g.H, g.W,
                                    (double)y + ps[0], (double)x + ps[1]);
       acc.x += v.x;
       acc.y += v.y;
     }
-    G[(size_t)j * HW + i] = acc;
+    Gj[i] = acc;
   }
 }
 
-hipError_t launch_probe_shift_acc(const DevGeom& g, float2* G, const float2* Pbuf, int k_first,
-                                  int Kc, hipStream_t st) {
+hipError_t launch_probe_shift_acc(const DevGeom& g, float2* G, const float2* Pbuf, int first,
+                                  int split, int k_first, int Kc, hipStream_t st) {
   const size_t HW = (size_t)g.H * g.W;
   const unsigned gx = (unsigned)std::min<size_t>((HW + kThreads - 1) / kThreads, 4096);
-  k_probe_shift_acc<<<dim3(gx, g.nd), kThreads, 0, st>>>(G, Pbuf, g, k_first, Kc);
+  k_probe_shift_acc<<<dim3(gx, g.nd, split), kThreads, 0, st>>>(G, Pbuf, g, first, k_first, Kc);
   return hipGetLastError();
 }
 
@@ -1083,6 +1190,12 @@ hipError_t launch_fill(float2* p, size_t n, float2 value, hipStream_t st) {
 
 hipError_t launch_fill_zero(float2* p, size_t n, hipStream_t st) {
   return launch_fill(p, n, make_float2(0.f, 0.f), st);
+}
+
+hipError_t launch_sum_slots(float2* G, int ns, size_t n, hipStream_t st) {
+  if (ns <= 1) return hipSuccess;
+  k_sum_slots<<<grid_for(n), kThreads, 0, st>>>(G, ns, n);
+  return hipGetLastError();
 }
 
 hipError_t launch_sum_frames(const float2* G, int nd, const float2* extra, float2* out, size_t n,
@@ -1130,6 +1243,10 @@ hipError_t launch_reduce_sum(const double* parts, size_t n, double* scratch, dou
   // two stages: up to kReduceParts workgroups of consecutive partials, then one
   const size_t g = std::max<size_t>(1, std::min<size_t>(kReduceParts, (n + 8191) / 8192));
   const size_t per = (n + g - 1) / g;
+  if (g == 1) {
+    k_reduce_sum<<<1, kThreads, 0, st>>>(parts, n, n, out);
+    return hipGetLastError();
+  }
   k_reduce_sum<<<(unsigned)g, kThreads, 0, st>>>(parts, n, per, scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
