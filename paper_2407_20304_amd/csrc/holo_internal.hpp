@@ -22,14 +22,6 @@ enum AngleCols {
   kD = 6,
   kScale = 7    // path length per step, 1 / max(|cos|, |sin|)
 };
-// Class of an angle in the transpose: its direction, taken as theta - pi
-// (-cos, -sin) when cos < 0 (the rows the transpose reads reversed), has
-// sin >= 0 (class 0) or sin < 0 (class 1).
-inline int adj_class(const double* a) {
-  const double s = a[kCos] < 0.0 ? -a[kSin] : a[kSin];
-  return s < 0.0 ? 1 : 0;
-}
-
 // Geometry and device tables as the kernels see them.
 struct DevGeom {
   int H, W, nd;
@@ -52,11 +44,11 @@ struct DevGeom {
   const float2* chirp2W;     // [2 nd + 1][2W], times 1/(2W)
   const float2* chirp2H;     // [2 nd + 1][2H], times 1/(2H)
   int col_tile;              // columns per pass-B workgroup (0: the default)
-  // Joseph plans store the sinogram rows of angles with cos < 0 with the
-  // bin axis reversed (as the angle theta - pi): pass D writes them so and
-  // the transpose reads them so, which makes cos >= 0 for every angle it sees
-  const double* ang;         // [n_angles][kAngleStride] plan angle table
-  int sino_mirror;
+  // the layout pass D writes the sinogram in: 1 (Joseph) in blocks of 64
+  // slices, [k][z / 64][re, im][(z / 8) % 8][bin][z % 8], with the slices'
+  // largest magnitudes raised in smax; 0 (Fourier-slice) in rows, S[k][z][bin]
+  int sino_blocked;
+  unsigned* smax;            // [H] bits of the largest |re|, |im| of every slice
 };
 
 // Fourier-slice projector (holo_fs.hip): gridding kernel taps per axis,
@@ -121,17 +113,17 @@ bool fft_size_supported(int n);
 bool col_tile_supported(int H, int tc);
 // Ray-sum tiling (see the kernels): forward angle-group size, slices and
 // bins per workgroup, staged rows per block and staged columns per row;
-// transpose slices per thread, angles per staged group and bins per staged
-// segment; slice blocking of the forward's volume copies.
+// transpose slices and threads per workgroup, bins per staged segment and power of two of the footprint weights; slice blocking of the
+// forward's volume copies.
 constexpr int kFwdNA = 4, kFwdZT = 64, kFwdNB = 16, kFwdYB = 2, kFwdSeg = 32;
-constexpr int kAdjZT = 16, kAdjNA = 4, kAdjSeg = 32;
+constexpr int kAdjZT = 64, kAdjBins = 26, kAdjThreads = 512, kAdjWScale = 14;
 constexpr int kAdjWin = 64;   // angles per transpose set-up window
 constexpr int kVolZB = 16;
-// Zero bins on each side of every row of the sinogram read by the transpose,
-// stored S[k][z][kAdjPad + bin]: a staged segment is then always valid
+// Zero bins on each side of every row of the sinogram read by the transpose
+// (bin i is stored at kAdjPad + i): a staged segment is then always valid
 // memory (segments wholly off the detector are moved into the padding,
 // which reads as zeros).
-constexpr int kAdjPad = kAdjSeg;
+constexpr int kAdjPad = 32;
 inline __host__ __device__ int sino_row(int W) { return W + 2 * kAdjPad; }
 // Zero columns on each side of every row of the forward's volume copies: a
 // staged row window is then always valid memory (windows wholly outside the
@@ -190,15 +182,14 @@ hipError_t launch_pass_d(const DevGeom& g, const float2* X, const float2* psi, f
 hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uTb, float2* psi,
                             const double* ang, const int2* groups, int g0, int ngroups, int c0,
                             int c1, int nb, hipStream_t st);
-// Transpose of the ray sums over angles k0 + [0, n0 + n1): S holds their rows
-// (row k - k0), ang the plan's whole angle table; ord0 / ord1 list the angles
-// of class 0 / 1 (sin >= 0 / < 0 once rows with cos < 0 are reversed) in
-// ascending order.
-hipError_t launch_radon_adj(const DevGeom& g, const float2* S, float2* gu, const double* ang,
-                            int k0, const int* ord0, int n0, const int* ord1, int n1,
-                            hipStream_t st);
+// Transpose of the ray sums over angles k0 .. k0 + K - 1: S holds their
+// sinogram in pass D's blocked layout (overwritten by its split form), ang
+// the plan's whole angle table, smax the slices' largest magnitudes.
+hipError_t launch_radon_adj(const DevGeom& g, float2* S, float2* gu, const double* ang, int k0,
+                            int K, const unsigned* smax, hipStream_t st);
+// (clears smax)
 hipError_t launch_block_volume(const DevGeom& g, const float2* u, float2* ub, float2* uTb,
-                               hipStream_t st);
+                               unsigned* smax, hipStream_t st);
 hipError_t launch_fill_zero(float2* p, size_t n, hipStream_t st);
 hipError_t launch_fill(float2* p, size_t n, float2 value, hipStream_t st);
 hipError_t launch_sum_frames(const float2* G, int nd, const float2* extra, float2* out,

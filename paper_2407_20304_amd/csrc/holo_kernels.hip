@@ -746,16 +746,19 @@ __global__ __launch_bounds__(kThreads) void k_frames_c(float2* __restrict__ X,
 // on the angle, so they are formed once for all of them.
 constexpr int kPassDAngles = 4;
 
+template <bool BLOCKED>
 __global__ __launch_bounds__(kThreads) void k_pass_d(const float2* __restrict__ X,
                                                      const float2* __restrict__ psi,
                                                      float2* __restrict__ S, DevGeom g,
                                                      int k_first, int Kc) {
   // A workgroup covers 16 rows x 16 padded bins, bins fastest, of the
-  // sinogram S[k][z][kAdjPad + s] (rows padded by kAdjPad zero bins on each
-  // side; with g.sino_mirror, rows of angles with cos < 0 are stored
-  // reversed, bin s at kAdjPad + W - 1 - s) for kPassDAngles consecutive
-  // angles.  Workgroups over the padding
-  // write its zeros.  The transposed resampling is separable, so its taps
+  // sinogram (rows padded by kAdjPad zero bins on each side) for
+  // kPassDAngles consecutive angles.  Workgroups over the padding write its
+  // zeros.  BLOCKED: the layout of the Joseph transpose,
+  // [k][z / 64][re, im][(z / 8) % 8][kAdjPad + s][z % 8]; the 16 x 16 results
+  // go through LDS so that each wave stores one 512-byte run, and the largest
+  // |re|, |im| of every slice is kept in g.smax.  Otherwise rows,
+  // S[k][z][kAdjPad + s].  The transposed resampling is separable, so its taps
   // are formed once per workgroup (once per angle with shifts): per plane,
   // the row taps of each of the 16 rows and the column taps of each of the
   // 16 bins.  Of the three candidates of an axis at most two adjacent ones
@@ -766,6 +769,8 @@ __global__ __launch_bounds__(kThreads) void k_pass_d(const float2* __restrict__ 
   static_assert(kMaxDist * 2 * SC <= kThreads, "one tap set per thread");
   __shared__ int s_d[kMaxDist][2 * SC][2];
   __shared__ float s_w[kMaxDist][2 * SC][2];
+  __shared__ float2 s_out[2][BLOCKED ? SC : 1][SC + 1];
+  float big = 0.f;
   const int H = g.H, W = g.W, Wp = sino_row(W);
   const int nsb = Wp / SC;
   const int z0 = (blockIdx.x / nsb) * ZR, sp0 = (blockIdx.x % nsb) * SC;
@@ -804,35 +809,54 @@ __global__ __launch_bounds__(kThreads) void k_pass_d(const float2* __restrict__ 
       }
       __syncthreads();
     }
-    // rows of angles with cos < 0 reversed for the Joseph transpose
-    const bool mir = g.sino_mirror && g.ang[(size_t)(k_first + k) * kAngleStride + kCos] < 0.0;
-    float2* out = S + ((size_t)k * H + z) * Wp + (mir ? Wp - 1 - sp : sp);
-    if (!inside) {
-      *out = make_float2(0.f, 0.f);
-      continue;
-    }
-    float ax = 0.f, ay = 0.f;
-    for (int j = 0; j < g.nd; ++j) {
-      const float2* Xj = X + ((size_t)k * g.nd + j) * H * W;
+    float2 h = make_float2(0.f, 0.f);
+    if (inside) {
+      float ax = 0.f, ay = 0.f;
+      for (int j = 0; j < g.nd; ++j) {
+        const float2* Xj = X + ((size_t)k * g.nd + j) * H * W;
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        const float wz = s_w[j][r][a];
-        const float2* Xr = Xj + (size_t)s_d[j][r][a] * W;
+        for (int a = 0; a < 2; ++a) {
+          const float wz = s_w[j][r][a];
+          const float2* Xr = Xj + (size_t)s_d[j][r][a] * W;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const float wt = wz * s_w[j][SC + c][b];
-          const float2 v = Xr[s_d[j][SC + c][b]];   // in range; weight 0 if unused
-          ax += wt * v.x;
-          ay += wt * v.y;
+          for (int b = 0; b < 2; ++b) {
+            const float wt = wz * s_w[j][SC + c][b];
+            const float2 v = Xr[s_d[j][SC + c][b]];   // in range; weight 0 if unused
+            ax += wt * v.x;
+            ay += wt * v.y;
+          }
         }
       }
+      const float2 ps = psi[((size_t)k * H + z) * W + s];
+      // conj(psi) g
+      const float cx = ps.x * ax + ps.y * ay;
+      const float cy = ps.x * ay - ps.y * ax;
+      // -i kappa (cx + i cy) = kappa cy - i kappa cx
+      h = make_float2(g.kappa * cy, -g.kappa * cx);
     }
-    const float2 ps = psi[((size_t)k * H + z) * W + s];
-    // conj(psi) g
-    const float cx = ps.x * ax + ps.y * ay;
-    const float cy = ps.x * ay - ps.y * ax;
-    // -i kappa (cx + i cy) = kappa cy - i kappa cx
-    *out = make_float2(g.kappa * cy, -g.kappa * cx);
+    if constexpr (BLOCKED) {
+      // (fmaxf would drop a NaN: compared as bits below)
+      const unsigned hb = max(__float_as_uint(fabsf(h.x)), __float_as_uint(fabsf(h.y)));
+      big = __uint_as_float(max(__float_as_uint(big), hb));
+      // two buffers by angle parity: the barrier of the next angle separates
+      // this angle's reads from the writes after it
+      s_out[k & 1][r][c] = h;
+      __syncthreads();
+      const int part = threadIdx.x >> 7, t8 = (threadIdx.x >> 6) & 1;
+      const int sc = (threadIdx.x >> 2) & 15, zr = 8 * t8 + 2 * (threadIdx.x & 3);
+      const float2 a = s_out[k & 1][zr][sc], b = s_out[k & 1][zr + 1][sc];
+      const size_t run = ((size_t)k * (H / kAdjZT) + z0 / kAdjZT) * 16 + part * 8 + (z0 / 8) % 8 + t8;
+      S[(run * Wp + sp0 + sc) * 4 + (threadIdx.x & 3)] =
+          part ? make_float2(a.y, b.y) : make_float2(a.x, b.x);
+    } else {
+      S[((size_t)k * H + z) * Wp + sp] = h;
+    }
+  }
+  if constexpr (BLOCKED) {
+    unsigned m = __float_as_uint(big);
+#pragma unroll
+    for (int o = 1; o < SC; o <<= 1) m = max(m, (unsigned)__shfl_xor((int)m, o, 64));
+    if (c == 0 && m > g.smax[z]) atomicMax(g.smax + z, m);
   }
 }
 
@@ -1136,7 +1160,10 @@ hipError_t launch_pass_c(const DevGeom& g, float2* X, const float2* psi, const f
 hipError_t launch_pass_d(const DevGeom& g, const float2* X, const float2* psi, float2* S,
                          int k_first, int Kc, hipStream_t st) {
   const dim3 grid((g.H / 16) * (sino_row(g.W) / 16), (Kc + kPassDAngles - 1) / kPassDAngles);
-  k_pass_d<<<grid, kThreads, 0, st>>>(X, psi, S, g, k_first, Kc);
+  if (g.sino_blocked)
+    k_pass_d<true><<<grid, kThreads, 0, st>>>(X, psi, S, g, k_first, Kc);
+  else
+    k_pass_d<false><<<grid, kThreads, 0, st>>>(X, psi, S, g, k_first, Kc);
   return hipGetLastError();
 }
 

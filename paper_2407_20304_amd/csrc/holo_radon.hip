@@ -6,15 +6,11 @@
 //                 LDS by LDS-direct loads (16 lanes cover the 64 slices of
 //                 one bin group, each thread owns 4 slices x 4 bins), fused
 //                 exp(i kappa p) epilogue
-//   radon_adj     transpose as a triangle-footprint gather over all angles
-//                 (a workgroup per 16 x 16 voxel tile and kAdjZT slices,
-//                 each thread a 2 x 2 voxel block and kAdjZT / 4 slices,
-//                 angles in two classes by the sign of sin), sinogram
+//   split_sino    the sinogram as pairs of half-precision terms, in place
+//   radon_adj     transpose as products on the matrix cores (a workgroup per
+//                 16 x 16 voxel tile and 64 slices, all angles), sinogram
 //                 segments staged in LDS per angle group by LDS-direct loads
-// Both are bound by VALU issue and LDS operand delivery, not by HBM: every
-// voxel is revisited once per angle.
-#include <type_traits>
-
+// None is bound by HBM: every voxel is revisited once per angle.
 #include "holo_internal.hpp"
 
 namespace holo {
@@ -26,7 +22,8 @@ namespace holo {
 // first and last brick column also clear the padding of their 16 rows.
 __global__ __launch_bounds__(kThreads) void k_block_volume(const float2* __restrict__ u,
                                                            float2* __restrict__ ub,
-                                                           float2* __restrict__ uTb, int W) {
+                                                           float2* __restrict__ uTb,
+                                                           unsigned* __restrict__ smax, int W) {
   constexpr int ZT = kVolZB, P = kFwdPad;
   // one 16 x 17 plane per slice, planes 274 elements apart: the write phase
   // reads down the slices (the 16 lanes of consecutive z at one position,
@@ -38,6 +35,8 @@ __global__ __launch_bounds__(kThreads) void k_block_volume(const float2* __restr
   const int nt = W / 16, Wf = vol_row(W);
   const int x0 = (blockIdx.x % nt) * 16, y0 = (blockIdx.x / nt) * 16;
   const int zb = blockIdx.y;
+  // the sinogram's slice maxima, which pass D raises, start at zero
+  if (blockIdx.x == 0 && threadIdx.x < ZT) smax[zb * ZT + threadIdx.x] = 0u;
   const size_t WW = (size_t)W * W, WWf = (size_t)W * Wf;
   // read along x (contiguous)
   for (int i = threadIdx.x; i < ZT * 256; i += kThreads) {
@@ -275,44 +274,118 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   }
 }
 
-// Transpose.  A workgroup owns a 16 x 16 voxel tile and kAdjZT slices; a
-// thread owns a 2 x 2 voxel block (an x pair in two neighbouring rows) and
-// a quarter of the slices (kAdjZT / 4, one slice group per wave).  It loops
-// over all angles in groups of kAdjNA (one wave loads each angle of a
-// group): the kAdjSeg bins of each slice that the tile projects onto are
-// copied straight from the sinogram into LDS, [angle][slice][bin], by
-// LDS-direct loads one group ahead of use (two group buffers); per slice a
-// thread then reads the four consecutive bins that carry its four voxels'
-// weights (8 bytes of LDS per voxel and slice).  The lanes of a wave read
-// bins of one 256-byte bin row: no bank conflicts.  The angles come in two
-// classes, each in a list of its own (ascending angle indices): after the
-// reversal of the rows with cos < 0, sin >= 0 (class 0) or sin < 0 (class
-// 1).  Within a class the lowest-projecting voxel of every block is the
-// same one, so each class runs a loop specialised for it; each class is
-// padded to whole groups with dummy angles whose segment is the zero
-// padding of a row.  Sinogram rows are zero-padded by kAdjPad bins, so a segment
-// is read without bounds checks.  A voxel projecting to fractional bin q
-// takes max(0, 1 - |i - q| / h) / h of bin i (h = max(|cos|, |sin|)) --
-// exactly the weight Joseph's interpolation gave it.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_radon_adj(const float2* __restrict__ S,
-                                                         float2* __restrict__ gu, DevGeom g,
-                                                         const double* __restrict__ ang,
-                                                         int k0, const int* __restrict__ ord0,
-                                                         int n0, const int* __restrict__ ord1,
-                                                         int n1) {
-  constexpr int ZT = kAdjZT, NA = kAdjNA, SEG = kAdjSeg, TW = kAdjWin;
-  constexpr int NBUF = 2;                           // group buffers (loads run 1 group ahead)
-  constexpr int GF2 = NA * ZT * SEG;                // float2 per staged group
-  constexpr int LPW = ZT * SEG / 128;               // LDS-direct loads (1 KB) per wave per group
-  static_assert(NA == kThreads / 64 && SEG == 32 && LPW == 4 && TW % NA == 0 && kAdjPad >= SEG,
-                "staging layout");
-  __shared__ float4 tile4[NBUF * GF2 / 2];
-  // Per-angle set-up for a window of TW angles, double-buffered by window
-  // parity: first staged bin, fractional bin of the tile corner relative to
-  // it, cos, sin, 1/h and 1/h^2.
-  __shared__ int s_sl[2][TW], s_row[2][TW];
-  __shared__ float s_f0[2][TW], s_c[2][TW], s_s[2][TW], s_ih[2][TW], s_ih2[2][TW];
-  const float2* tile = reinterpret_cast<const float2*>(tile4);
+// ---------------------------------------------------------------------------
+// Transpose on the matrix cores
+// ---------------------------------------------------------------------------
+
+// The transpose is a contraction: a 4 x 4 block of voxels projects at one
+// angle onto at most 7 consecutive bins (its positions span at most
+// 3 sqrt(2), and each footprint max(0, 1 - |i - q| / h) / h is at most two
+// bins wide), the same ones for every slice, so
+//   g[16 voxels][slices x (re, im)] += w[16 voxels][4 angles x 8 bins]
+//                                      h[4 angles x 8 bins][slices x (re, im)]
+// is one 16 x 16 x 32 product per 8 slices.  Operands are single-precision
+// numbers split into two half-precision terms each, x = x1 + x2 (the second
+// term the rounded remainder: together 22 to 24 bits), multiplied as
+// w1 h1 + w1 h2 + w2 h1 with single-precision sums; the dropped w2 h2 is
+// below the last bit kept.  On the vector units the same sums took 8.6
+// instructions and 8 bytes of LDS reads per voxel, slice and angle against
+// 4 bytes and 24 products of 16 x 16 x 32 per 16 x 64 x 4 of them here: 345
+// -> 201 ms at 1024^3 x 1800 angles, conversion included.  Every slice of h is scaled by a power of two
+// (its largest value to 2^14 .. 2^15) and the weights by 2^kAdjWScale, so
+// that both terms are normal numbers down to 2^-17 of the largest value; the
+// result is scaled back exactly.
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+// Power of two that brings a largest magnitude (its bits) to 2^14 .. 2^15,
+// within what a float holds together with its inverse; 1 for zero, infinity
+// and NaN.
+__device__ __forceinline__ int split_exponent(unsigned bits) {
+  if (bits == 0u || bits >= 0x7f800000u) return 0;
+  return min(14 - ((int)(bits >> 23) - 127), 120);
+}
+
+__device__ __forceinline__ unsigned pack_half2(_Float16 a, _Float16 b) {
+  half2v v = {a, b};
+  return __builtin_bit_cast(unsigned, v);
+}
+
+// The sinogram as pass D leaves it to the split form that k_radon_adj stages,
+// in the same memory.  Both are [k][z / 64][2][(z / 8) % 8][bin][z % 8]
+// words of 32 bits: pass D puts the real part in half 0 and the imaginary
+// part in half 1, the split form the first terms of both (two half-precision
+// numbers) in half 0 and the second terms in half 1.  The two words of a
+// sample are read and written by one thread.  Bound by HBM: 8 bytes read and
+// written per bin and slice.
+__global__ __launch_bounds__(kThreads) void k_split_sino(unsigned* __restrict__ S,
+                                                         const unsigned* __restrict__ smax,
+                                                         size_t n, int Wp, int nzb) {
+  // thread: 4 consecutive slices of one bin
+  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i >= n) return;
+  const size_t half = (size_t)8 * Wp * 2;            // threads per half block
+  const size_t blk = i / half, o = i % half;         // (k, z / 64), offset in it
+  const int z = (int)(blk % nzb) * kAdjZT + (int)(o / (2 * Wp)) * 8 + (int)(o & 1) * 4;
+  float4* lo = reinterpret_cast<float4*>(S) + blk * 2 * half + o;
+  float4* hi = lo + half;
+  const float4 re = *lo, im = *hi;
+  const float x[4] = {re.x, re.y, re.z, re.w}, y[4] = {im.x, im.y, im.z, im.w};
+  unsigned a[4], b[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float sc = ldexpf(1.0f, split_exponent(smax[z + c]));
+    const float u = x[c] * sc, v = y[c] * sc;
+    const _Float16 u1 = (_Float16)u, v1 = (_Float16)v;
+    a[c] = pack_half2(u1, v1);
+    b[c] = pack_half2((_Float16)(u - (float)u1), (_Float16)(v - (float)v1));
+  }
+  *reinterpret_cast<uint4*>(lo) = make_uint4(a[0], a[1], a[2], a[3]);
+  *reinterpret_cast<uint4*>(hi) = make_uint4(b[0], b[1], b[2], b[3]);
+}
+
+// Per-angle constants of a tile: fractional bin of its corner voxel relative
+// to the first staged bin, the steps per voxel in x and y, the lowest corner
+// of a 4 x 4 block relative to its first voxel, footprint 1/h and 1/h^2
+// (times 2^kAdjWScale), the first staged bin and the sinogram row.
+struct AdjAngle {
+  float f0, c, s, mn;
+  float ih, ih2;
+  int bin0, row;
+};
+
+// A workgroup of 8 waves owns 16 x 16 voxels and 64 slices; wave w the two
+// 4 x 4 blocks at x = 4 (w % 4), y = 8 (w / 4) and y + 4.  It walks the
+// angles in groups of 4 (one per 16 lanes of a wave): the bins of each angle
+// that the tile projects onto (its corners span at most 15 sqrt(2) bins) are
+// copied from the split sinogram into LDS by LDS-direct loads two
+// groups ahead (three buffers of 52 KB).  Per block a lane forms the 8 footprint
+// weights of its voxel and angle (single precision, positions as small
+// offsets from double-precision bases) and splits them; the sinogram's
+// operand comes from transposing LDS reads: 16 lanes read 4 bins x 16 columns
+// stored with the columns fastest, and each lane receives the 4 bins of one
+// column (two-address reads of single words took 4.4 clocks of LDS per 512
+// bytes, these 2.1 in the counters, and any first bin is aligned).  In LDS the 32 bytes (16 columns) of one bin alternate between two
+// angles: the 4 bins of two angles that one pass of a read serves lie on
+// different banks wherever their windows start.  Partial sums of 32 angles
+// are added into outer sums.
+__global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __restrict__ S,
+                                                              float2* __restrict__ gu, DevGeom g,
+                                                              const double* __restrict__ ang,
+                                                              int k0, int K,
+                                                              const unsigned* __restrict__ smax) {
+  constexpr int NA = 4, NB = kAdjBins, TW = kAdjWin;
+  constexpr int NT = kAdjZT / 8;                    // 16-column tiles of the result
+  // LDS of a group: [angle / 2][tile][half][bin][angle % 2][16 half-precision]
+  constexpr int ROWS = 2 * NT * 2 * NB;             // of 64 bytes
+  constexpr int LOADS = ROWS / 16;                  // LDS-direct loads (1 KB) per group
+  constexpr int LPW = (LOADS + 7) / 8;              // per wave
+  static_assert(ROWS % 32 == 0 && LOADS > 8 * (LPW - 1) && NB % 2 == 0 && NB <= kAdjPad, "staging");
+  __shared__ uint4 tile4[3 * ROWS * 4];
+  __shared__ AdjAngle s_ang[2][TW];
   const int W = g.W, H = g.H, Wp = sino_row(W);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   // logical order: slice blocks slowest; within one, the tiles in square
@@ -325,201 +398,226 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
   const int tl = L % (nt * nt), grp = tl / (GS * GS), in_grp = tl % (GS * GS);
   const int x0 = ((grp % (nt / GS)) * GS + in_grp % GS) * 16;
   const int y0 = ((grp / (nt / GS)) * GS + in_grp / GS) * 16;
-  // thread: voxels (x, y), (x + 1, y), (x, y + 1), (x + 1, y + 1),
-  // x = x0 + 2 px, y = y0 + 2 py, and the 4 slices of slice group sg (its
-  // wave) of the block
-  const int px = threadIdx.x & 7, py = (threadIdx.x >> 3) & 7, sg = threadIdx.x >> 6;
-  const int x = x0 + 2 * px, y = y0 + 2 * py;
-  const int z0 = (L / (nt * nt)) * ZT;
-  const double X0 = (double)x0 - g.cW, X1 = X0 + 15.0;
-  const double Y0 = (double)y0 - g.cW, Y1 = Y0 + 15.0;
+  const int zb = L / (nt * nt), nzb = H / kAdjZT;
+  const double X0 = (double)x0 - g.cW, Y0 = (double)y0 - g.cW;
+  const int ng = (K + NA - 1) / NA;
 
-  // Position p of the angle sequence: class 0's list padded to a multiple of
-  // NA, then class 1's.  Returns the angle (a dummy repeats its class's last
-  // angle) and whether it is a dummy.
-  const int G0 = (n0 + NA - 1) / NA, G1 = (n1 + NA - 1) / NA;
-  const int ng = G0 + G1, Kp = ng * NA;
-  auto angle_at = [&](int p, bool& dummy) {
-    if (p < G0 * NA) {
-      dummy = p >= n0;
-      return ord0[min(p, n0 - 1)];
-    }
-    p -= G0 * NA;
-    dummy = p >= n1;
-    return ord1[min(p, n1 - 1)];
-  };
-
-  // Set-up of position w * TW + t for threads t < TW, in double precision: the
-  // first staged bin is the lowest projection of the tile's corners minus two
-  // or three bins of margin (even, so each lane's bin pair is 16-byte
-  // aligned), moved into [-kAdjPad, W + kAdjPad - SEG] (a segment
-  // outside that range lies wholly off the detector, and the padding it is
-  // moved to holds zeros); a voxel's fractional bin relative to it is
-  // f0 + dx cos + dy sin, a small number that single precision holds to
-  // ~1e-6 of a bin.
+  // Constants of angles [w TW, (w + 1) TW) by threads t < TW, in double
+  // precision.  The first staged bin is the tile's lowest projection, moved
+  // into [-kAdjPad, W + kAdjPad - NB] (a segment outside that range lies
+  // wholly off the detector, and the padding it is moved to holds zeros); so
+  // are those of the angles past the last, with weight 0.
   auto setup_window = [&](int w) {
-    const int slot = w & 1, t = threadIdx.x;
+    const int t = threadIdx.x;
     if (t < TW) {
-      bool dummy;
-      const int kk = angle_at(min(w * TW + t, Kp - 1), dummy);
-      const double* ap = ang + (size_t)kk * kAngleStride;
-      // an angle with cos < 0 has its row stored reversed: it is the angle
-      // theta - pi, direction (-cos, -sin), positions W - 1 - q
-      const bool mir = ap[kCos] < 0.0;
-      const double C = mir ? -ap[kCos] : ap[kCos], Sn = mir ? -ap[kSin] : ap[kSin];
-      const double ih = ap[kInvH];
-      const double cq = mir ? (double)(W - 1) - g.cW : g.cW;
-      const double q0 = cq + X0 * C + Y0 * Sn;
-      int sl = (int)floor(cq + fmin(X0 * C, X1 * C) + fmin(Y0 * Sn, Y1 * Sn)) - 2;
-      sl -= sl & 1;                                     // even: 16-byte aligned bin pairs
-      sl = min(max(sl, -kAdjPad), W + kAdjPad - SEG);
-      // a dummy reads the zero padding left of its row; its weights are
-      // zero there too (its taps fall far right of the segment)
-      if (dummy) sl = -kAdjPad;
-      s_sl[slot][t] = sl;
-      s_row[slot][t] = kk - k0;
-      s_f0[slot][t] = (float)(q0 - (double)sl);
-      s_c[slot][t] = (float)C;
-      s_s[slot][t] = (float)Sn;
-      s_ih[slot][t] = (float)ih;
-      s_ih2[slot][t] = (float)(ih * ih);
+      const int ka = min(w * TW + t, K - 1);
+      const bool live = w * TW + t < K;
+      const double* ap = ang + (size_t)(k0 + ka) * kAngleStride;
+      const double C = ap[kCos], Sn = ap[kSin], ih = live ? ap[kInvH] : 0.0;
+      const double q0 = g.cW + X0 * C + Y0 * Sn;
+      int sl = (int)floor(q0 + 15.0 * fmin(C, 0.0) + 15.0 * fmin(Sn, 0.0));
+      sl = live ? min(max(sl, -kAdjPad), W + kAdjPad - NB) : -kAdjPad;
+      AdjAngle a;
+      a.f0 = (float)(q0 - (double)sl);
+      a.c = (float)C;
+      a.s = (float)Sn;
+      a.mn = (float)(3.0 * fmin(C, 0.0) + 3.0 * fmin(Sn, 0.0));
+      const double ws = (double)(1 << kAdjWScale);
+      a.ih = (float)(ih * ws);
+      a.ih2 = (float)(ih * ih * ws);
+      a.bin0 = sl + kAdjPad;
+      a.row = ka;
+      s_ang[w & 1][t] = a;
     }
   };
 
-  // The sinogram is S[k][z][kAdjPad + bin].  Load i of wave a (angle a of the
-  // group) moves 1 KB: lane l brings bins 2 (l % 16) and 2 (l % 16) + 1 of
-  // the segment of slice 4 i + l / 16, which lands at byte 16 l of the
-  // load's 1 KB -- the [slice][bin] layout of that angle.  Issued as inline
+  // Loads of a group: load i of wave w brings rows 16 (8 i + w) .. + 15 of
+  // LDS; lane l the half l % 2 (8 columns) of the 32 bytes of angle parity
+  // (l / 2) % 2 of row l / 4.  The global word of each load relative to the
+  // angle's first bin is formed once.  The loads of the next group are
+  // spread over the products of the current one: a wave waits at a load
+  // until the memory pipeline takes it, and issued together at the start of
+  // a group the 52 loads of 1 KB held every wave up (512^3 x 900 angles: 14.9
+  // ms with one group ahead, 13.6 spread out, 12.7 spread out and two groups
+  // ahead, 10.6 without any; 6.6 is the products alone).  Issued as inline
   // assembly (M0 = LDS destination) so the compiler adds no waits of its
   // own; the loop waits for them explicitly.
-  const size_t HWp = (size_t)H * Wp;
-  const float2* Sl = S + (size_t)(z0 + (lane >> 4)) * Wp + kAdjPad + 2 * (lane & 15);
-  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float4*)tile4;
-  auto issue = [&](int gidx) {
-    const int p0 = gidx * NA;
-    const int sl = __builtin_amdgcn_readfirstlane(s_sl[(p0 / TW) & 1][p0 % TW + wave]);
-    const int row = __builtin_amdgcn_readfirstlane(s_row[(p0 / TW) & 1][p0 % TW + wave]);
-    const float2* src = Sl + (size_t)row * HWp + sl;
-    const unsigned dst = __builtin_amdgcn_readfirstlane(
-        lds0 + (unsigned)((((gidx % NBUF) * GF2) + wave * ZT * SEG) * 8));
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint4*)tile4;
+  unsigned goff[LPW];
 #pragma unroll
-    for (int i = 0; i < LPW; ++i)
+  for (int i = 0; i < LPW; ++i) {
+    const int row = min(16 * (8 * i + wave) + (lane >> 2), ROWS - 1) % (ROWS / 2);
+    const int bin = row % NB, th = row / NB;        // th = tile * 2 + half
+    goff[i] = (unsigned)(((th & 1) * 8 + (th >> 1)) * Wp + bin) * 8u + 4u * (lane & 1);
+  }
+  const size_t angw = (size_t)nzb * Wp * 128;       // words per angle
+  const unsigned* Sz = S + (size_t)zb * (Wp * 128);
+  const unsigned* src0 = S;                         // first bins of the lane's two angles
+  const unsigned* src1 = S;
+  unsigned dst = 0;
+  auto issue_begin = [&](int gi, unsigned buf) {
+    const AdjAngle* a = &s_ang[((gi * NA) / TW) & 1][(gi * NA) % TW + ((lane >> 1) & 1)];
+    src0 = Sz + (size_t)a[0].row * angw + 8u * (unsigned)a[0].bin0;
+    src1 = Sz + (size_t)a[2].row * angw + 8u * (unsigned)a[2].bin0;
+    dst = __builtin_amdgcn_readfirstlane(lds0 + buf + (unsigned)(wave * 1024));
+  };
+  auto issue = [&](int i) {
+    constexpr int HALF = LOADS / 2;                 // loads of angles 0 and 1
+    if (8 * i + 8 <= LOADS || 8 * i + wave < LOADS) {
+      const unsigned* src = (8 * i + 8 <= HALF ? src0 : 8 * i >= HALF ? src1
+                             : 8 * i + wave < HALF ? src0 : src1) + goff[i];
       asm volatile(
           "s_mov_b32 m0, %0\n\t"
           "s_nop 0\n\t"
           "global_load_lds_dwordx4 %1, off"
           :
-          : "s"(dst + 1024u * i), "v"(src + (size_t)4 * i * Wp)
+          : "s"(dst + 8192u * i), "v"(src)
           : "memory", "m0");
+    }
   };
 
-  constexpr int ZS = ZT / 4;                        // slices per thread
-  static_assert(ZS == 4 && NA == 4, "slice group per wave");
-  // accumulators [voxel v = dx + 2 dy][slice]
-  float ax[4][ZS], ay[4][ZS];
-  float ox[4][ZS], oy[4][ZS];
+  // lane: voxel m of a block (A rows) or column m of a tile (B columns), angle
+  // ga of the group
+  const int m = lane & 15, ga = lane >> 4;
+  const int bx = 4 * (wave & 3), by = 8 * (wave >> 2);
+  const float vx = (float)(bx + (m & 3)), vy = (float)(by + (m >> 2));
+  const float fbx = (float)bx, fby = (float)by;
+  float4v acc[2][NT], out[2][NT];
 #pragma unroll
-  for (int v = 0; v < 4; ++v)
+  for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int i = 0; i < ZS; ++i) { ax[v][i] = ay[v][i] = 0.f; ox[v][i] = oy[v][i] = 0.f; }
+    for (int t = 0; t < NT; ++t) { acc[b][t] = (float4v)(0.f); out[b][t] = (float4v)(0.f); }
+
+  // Operands of block b of group gi: the lane's 8 weights, and the LDS
+  // address of its words of the block's first pair.
+  half8 a1, a2;
+  unsigned bp;
+  const unsigned lp = lds0 + (unsigned)((ga >> 1) * (ROWS * 32) + (m >> 2) * 64 + (ga & 1) * 32 + (m & 3) * 8);
+  float minus1 = -1.0f;
+  asm volatile("" : "+s"(minus1));                  // (keeps the mixed-precision FMA below)
+  auto weights = [&](int gi, int b, unsigned buf) {
+    const int p0 = gi * NA;
+    const AdjAngle A = s_ang[(p0 / TW) & 1][p0 % TW + ga];
+    // the block's lowest bin, and the voxel's position above it
+    const float low = fmaf(fby + 4.f * b, A.s, fmaf(fbx, A.c, A.f0) + A.mn);
+    const float jf = fminf(fmaxf(floorf(low), 0.f), (float)(NB - 8));
+    const float d = fmaf(vy + 4.f * b, A.s, fmaf(vx, A.c, A.f0)) - jf;
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+      const float u = fmaxf(0.0f, fmaf(-fabsf(d - (float)i), A.ih2, A.ih));
+      const float v = fmaxf(0.0f, fmaf(-fabsf(d - (float)(i + 1)), A.ih2, A.ih));
+      // one packed conversion, whose halves the remainders are then taken from
+      unsigned pu = pack_half2((_Float16)u, (_Float16)v);
+      asm volatile("" : "+v"(pu));
+      const half2v p = __builtin_bit_cast(half2v, pu);
+      const half2v r = {(_Float16)fmaf((float)p[0], minus1, u), (_Float16)fmaf((float)p[1], minus1, v)};
+      a1[i] = p[0];
+      a1[i + 1] = p[1];
+      a2[i] = r[0];
+      a2[i + 1] = r[1];
+    }
+    bp = lp + buf + 64u * (unsigned)(int)jf;
+  };
 
   constexpr int GPW = TW / NA;                      // groups per set-up window
   setup_window(0);
   __syncthreads();
-  issue(0);
-  // One group of NA angles of one class.
-  auto group = [&](int gi, auto sneg) {
-    constexpr bool SNEG = decltype(sneg)::value;
-    const int p0 = gi * NA;
-    // this wave's loads of group gi are complete and its LDS reads of group
-    // gi - 1 have returned; the barrier publishes group gi of every wave,
-    // retires group gi - 1 (whose buffer the loads of gi + 1 reuse) and the
-    // set-up window written below
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  // LDS offsets of the buffers of groups gi, gi + 1 and gi + 2
+  constexpr unsigned BUF = ROWS * 64;
+  unsigned buf0 = 0, buf1 = BUF, buf2 = 2 * BUF;
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    issue_begin(min(n, ng - 1), n * BUF);
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) issue(i);
+  }
+  weights(0, 0, 0);
+  for (int gi = 0; gi < ng; ++gi) {
+    // this wave's loads of group gi are complete (those of group gi + 1, at
+    // least LPW - 1, may be in flight) and its LDS reads of group gi - 1 have
+    // returned; the barrier publishes group gi of every wave, retires group
+    // gi - 1 (whose buffer the loads of gi + 2 reuse) and the set-up window
+    // written below
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPW - 1) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (gi + 1 < ng) issue(gi + 1);
-    // the next window's set-up, written two groups before its first group
-    // is issued, into the slot of the window before the current one
-    if ((gi + 2) % GPW == 0 && (gi + 2) * NA < Kp) setup_window((gi + 2) / GPW);
-    const int slot = (p0 / TW) & 1, base = p0 % TW;
-    const float2* gb = tile + (gi % NBUF) * GF2;
-    // One angle.  Its row has cos >= 0 (rows of angles with cos < 0 are
-    // stored reversed), so the block's lowest fractional bin q belongs to
-    // voxel (x, y) in class 0 and to (x, y + 1) in class 1 (SNEG); the
-    // others lie at q + cos (the x neighbour of the lowest), q + |sin| (its
-    // y neighbour) and q + cos + |sin| (the opposite corner), with
-    // 1 <= cos + |sin| <= sqrt(2).  Every bin with a nonzero weight
-    // (|i - q'| < h <= 1) is one of jm .. jm + 3, jm = floor(q): bins jm,
-    // jm + 1 for the lowest voxel, jm .. jm + 2 for its two neighbours and
-    // jm + 1 .. jm + 3 for the opposite corner; the weight is the footprint
-    // max(0, 1/h - |i - q'| / h^2).
-    constexpr int VL = SNEG ? 2 : 0, VX = SNEG ? 3 : 1, VY = SNEG ? 0 : 2, VXY = SNEG ? 1 : 3;
-#pragma unroll 1
-    for (int a = 0; a < NA; ++a) {
-      const float ih = s_ih[slot][base + a], ih2 = s_ih2[slot][base + a];
-      const float c = s_c[slot][base + a], sn = s_s[slot][base + a];
-      const float as = SNEG ? -sn : sn;
-      const float q = fmaf((float)(2 * py + (SNEG ? 1 : 0)), sn,
-                           fmaf((float)(2 * px), c, s_f0[slot][base + a]));
-      const int jm = min(max((int)floorf(q), 0), SEG - 4);
-      const float d = q - (float)jm;                   // lowest voxel relative to bin jm
-      auto wt = [&](float dist) { return fmaxf(0.0f, fmaf(-fabsf(dist), ih2, ih)); };
-      const float dX = d + c, dY = d + as, dXY = dX + as;
-      const float wL0 = wt(d), wL1 = wt(1.0f - d);
-      const float wX0 = wt(dX), wX1 = wt(1.0f - dX), wX2 = wt(2.0f - dX);
-      const float wY0 = wt(dY), wY1 = wt(1.0f - dY), wY2 = wt(2.0f - dY);
-      const float wXY1 = wt(1.0f - dXY), wXY2 = wt(2.0f - dXY), wXY3 = wt(3.0f - dXY);
-      const float2* tp = gb + a * ZT * SEG + sg * ZS * SEG + jm;
-      // software pipeline: the four bins of slice i + LA are requested
-      // before slice i is accumulated
-      constexpr int LA = 1;
-      float2 r[ZS][4];
-      auto fetch = [&](int i) {
-        const float2* t = tp + i * SEG;
+    // (past the last group: its loads again, into an idle buffer)
+    issue_begin(min(gi + 2, ng - 1), buf2);
+    // the next window's set-up, written three groups before its first group
+    // is used, into the slot of the window before the current one
+    if ((gi + 3) % GPW == 0 && gi + 3 < ng) setup_window((gi + 3) / GPW);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) r[i][b] = t[b];
+    for (int b = 0; b < 2; ++b) {
+      // The operands of tile t + LA are requested before tile t is
+      // multiplied, and the next block's weights are formed between the
+      // products.
+      constexpr int LA = 2;
+      const half8 w1 = a1, w2 = a2;
+      auto* wp = (__attribute__((address_space(3))) short4v*)(uintptr_t)bp;
+      half8 h1[NT], h2[NT];
+      auto read8 = [&](int o) {                      // o: in 8 bytes; 8 bins of a column
+        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(wp + o);
+        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(wp + o + 32);
+        return __builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      };
+      auto fetch = [&](int t) {
+        h1[t] = read8((2 * t) * NB * 8);
+        h2[t] = read8((2 * t + 1) * NB * 8);
       };
 #pragma unroll
-      for (int i = 0; i < LA; ++i) fetch(i);
+      for (int t = 0; t < LA; ++t) fetch(t);
+      // (the last group's next weights are formed from the window's last
+      // entries again and not used)
+      weights(b == 0 ? gi : min(gi + 1, ng - 1), 1 - b, b == 0 ? buf0 : buf1);
 #pragma unroll
-      for (int i = 0; i < ZS; ++i) {
-        if (i + LA < ZS) fetch(i + LA);
-        const float2 r0 = r[i][0], r1 = r[i][1], r2 = r[i][2], r3 = r[i][3];
-        ax[VL][i] = fmaf(wL1, r1.x, fmaf(wL0, r0.x, ax[VL][i]));
-        ay[VL][i] = fmaf(wL1, r1.y, fmaf(wL0, r0.y, ay[VL][i]));
-        ax[VX][i] = fmaf(wX2, r2.x, fmaf(wX1, r1.x, fmaf(wX0, r0.x, ax[VX][i])));
-        ay[VX][i] = fmaf(wX2, r2.y, fmaf(wX1, r1.y, fmaf(wX0, r0.y, ay[VX][i])));
-        ax[VY][i] = fmaf(wY2, r2.x, fmaf(wY1, r1.x, fmaf(wY0, r0.x, ax[VY][i])));
-        ay[VY][i] = fmaf(wY2, r2.y, fmaf(wY1, r1.y, fmaf(wY0, r0.y, ay[VY][i])));
-        ax[VXY][i] = fmaf(wXY3, r3.x, fmaf(wXY2, r2.x, fmaf(wXY1, r1.x, ax[VXY][i])));
-        ay[VXY][i] = fmaf(wXY3, r3.y, fmaf(wXY2, r2.y, fmaf(wXY1, r1.y, ay[VXY][i])));
+      for (int t = 0; t < NT; ++t) {
+        if (t + LA < NT) fetch(t + LA);
+        if ((8 * b + t) % 2 == 1 && (8 * b + t) / 2 < LPW) issue((8 * b + t) / 2);
+        const half8 x1 = h1[t], x2 = h2[t];
+        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2, x1, acc[b][t], 0, 0, 0);
+        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1, x2, acc[b][t], 0, 0, 0);
+        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1, x1, acc[b][t], 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < 3 * NT; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // VALU
       }
     }
-    // two-level single-precision sums: partials of up to 8 NA angles are
-    // added into the outer sums
-    if ((gi & 7) == 7 || gi + 1 >= ng) {
+    // (formed above, not sunk below the branch)
+    asm volatile("" : "+v"(a1), "+v"(a2), "+v"(bp));
+    const unsigned next = buf0;
+    buf0 = buf1;
+    buf1 = buf2;
+    buf2 = next;
+    // two-level single-precision sums: partials of up to 32 angles
+    if ((gi & 7) == 7 || gi + 1 == ng) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int i = 0; i < ZS; ++i) {
-          ox[v][i] += ax[v][i];
-          oy[v][i] += ay[v][i];
-          ax[v][i] = ay[v][i] = 0.f;
-        }
+        for (int t = 0; t < NT; ++t) { out[b][t] += acc[b][t]; acc[b][t] = (float4v)(0.f); }
     }
-  };
-  for (int gi = 0; gi < G0; ++gi) group(gi, std::integral_constant<bool, false>());
-  for (int gi = G0; gi < ng; ++gi) group(gi, std::integral_constant<bool, true>());
-  const size_t WW = (size_t)W * W;
-#pragma unroll
-  for (int i = 0; i < ZS; ++i) {
-    float2* o = gu + (size_t)(z0 + sg * ZS + i) * WW + (size_t)y * W + x;
-#pragma unroll
-    for (int dy = 0; dy < 2; ++dy)
-      *reinterpret_cast<float4*>(o + (size_t)dy * W) =
-          make_float4(ox[2 * dy][i], oy[2 * dy][i], ox[2 * dy + 1][i], oy[2 * dy + 1][i]);
   }
+  // no load may arrive in LDS after the workgroup has ended
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // result layout: lane holds column n = m (slice 8 t + n / 2, re or im) of
+  // rows 4 ga .. 4 ga + 3: voxels bx .. bx + 3 of the block's row ga.  Lanes
+  // n and n ^ 1 exchange halves, so each stores two complex voxels.
+  const size_t WW = (size_t)W * W;
+  const bool im = (m & 1) != 0;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int z = zb * kAdjZT + 8 * t + (m >> 1);
+      const float sc = ldexpf(1.0f, -split_exponent(smax[z]) - kAdjWScale);
+      const float4v v = out[b][t] * sc;
+      const float s0 = im ? v[0] : v[2], s1 = im ? v[1] : v[3];
+      const float r0 = __shfl_xor(s0, 1, 64), r1 = __shfl_xor(s1, 1, 64);
+      const float4 o = im ? make_float4(r0, v[2], r1, v[3]) : make_float4(v[0], r0, v[1], r1);
+      float2* dst = gu + (size_t)z * WW + (size_t)(y0 + by + 4 * b + ga) * W + x0 + bx + (im ? 2 : 0);
+      *reinterpret_cast<float4*>(dst) = o;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -540,20 +638,24 @@ hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uT
   return hipGetLastError();
 }
 
-hipError_t launch_radon_adj(const DevGeom& g, const float2* S, float2* gu, const double* ang,
-                            int k0, const int* ord0, int n0, const int* ord1, int n1,
-                            hipStream_t st) {
-  // the kernel reads the rows of angles with cos < 0 reversed
-  if (!g.sino_mirror || n0 < 0 || n1 < 0 || n0 + n1 < 1) return hipErrorInvalidValue;
-  const unsigned n = (unsigned)(g.W / 16) * (unsigned)(g.W / 16) * (unsigned)(g.H / kAdjZT);
-  k_radon_adj<<<n, kThreads, 0, st>>>(S, gu, g, ang, k0, ord0, n0, ord1, n1);
+hipError_t launch_radon_adj(const DevGeom& g, float2* S, float2* gu, const double* ang, int k0,
+                            int K, const unsigned* smax, hipStream_t st) {
+  if (K < 1 || g.H % kAdjZT != 0 || g.W % 16 != 0) return hipErrorInvalidValue;
+  unsigned* Sw = reinterpret_cast<unsigned*>(S);
+  const int Wp = sino_row(g.W), nzb = g.H / kAdjZT;
+  const size_t ns = (size_t)K * nzb * Wp * 16;
+  k_split_sino<<<(unsigned)((ns + kThreads - 1) / kThreads), kThreads, 0, st>>>(Sw, smax, ns, Wp, nzb);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const unsigned n = (unsigned)(g.W / 16) * (unsigned)(g.W / 16) * (unsigned)nzb;
+  k_radon_adj<<<n, kAdjThreads, 0, st>>>(Sw, gu, g, ang, k0, K, smax);
   return hipGetLastError();
 }
 
 hipError_t launch_block_volume(const DevGeom& g, const float2* u, float2* ub, float2* uTb,
-                               hipStream_t st) {
+                               unsigned* smax, hipStream_t st) {
   const dim3 grid((g.W / 16) * (g.W / 16), g.H / kVolZB);
-  k_block_volume<<<grid, kThreads, 0, st>>>(u, ub, uTb, g.W);
+  k_block_volume<<<grid, kThreads, 0, st>>>(u, ub, uTb, smax, g.W);
   return hipGetLastError();
 }
 
