@@ -77,8 +77,11 @@ struct holo_plan {
   hipEvent_t ov_ev[5] = {};
   std::vector<float> fs_dinv;
   std::vector<int> fs_sorted, fs_bins;
-  size_t off_fsdinv = 0, off_fssorted = 0, off_fsbins = 0;
-  size_t off_fsG = 0, off_fsA = 0;
+  std::vector<FsItem> fs_items;             // workgroups of the transpose's spread
+  int fs_parts = 0;                         // partial tiles among them
+  int fs_batch = 1;                         // slabs per launch
+  size_t off_fsdinv = 0, off_fssorted = 0, off_fsbins = 0, off_fsitems = 0;
+  size_t off_fsG = 0, off_fsA = 0, off_fsP = 0;
   bool any_xwalk = false;
   // forward ray-sum angle groups: consecutive angles of one walk direction
   // whose staged row windows fit (first, count); group_of[k] = group index
@@ -171,6 +174,7 @@ static void build_fs_tables(holo_plan* P) {
     while (pos < P->n_angles && tm[P->fs_sorted[pos]] < lo) ++pos;
     P->fs_bins[b] = b == kFsBins ? P->n_angles : pos;
   }
+  fs_build_items(W, P->n_angles, P->fs_items, P->fs_parts);
 }
 
 // Can angles [a, b) share the staged row windows of the forward ray sums?
@@ -268,9 +272,18 @@ static void layout_workspace(holo_plan* P) {
   // Fourier-slice projector: the grids of one slab and its polar samples
   const bool fs = P->projector == HOLO_PROJECTOR_FOURIER;
   const size_t M = 2 * (size_t)P->W;
-  P->off_fsG = o; o = align_up(o + (fs ? (size_t)kFsSlab * M * M * sizeof(float2) : 0));
+  // slabs per launch: one at 512 px and above (67 MB of grids); below that as
+  // many as take as much, since a single one leaves most of the chip idle
+  // (128 px: 128 workgroups of 128 threads in a row pass)
+  const size_t gb = (size_t)kFsSlab * M * M * sizeof(float2);
+  P->fs_batch = (int)std::max<size_t>(
+      1, std::min<size_t>((size_t)P->H / P->fs_slab, ((size_t)1 << 26) / gb));
+  const size_t nb = fs ? (size_t)P->fs_batch : 0;
+  P->off_fsG = o; o = align_up(o + nb * gb);
   P->off_fsA = o;
-  o = align_up(o + (fs ? (size_t)kFsSlab * P->n_angles * (P->W + 2) * sizeof(float2) : 0));
+  o = align_up(o + nb * kFsSlab * P->n_angles * (P->W + 1) * sizeof(float2));
+  P->off_fsP = o;
+  o = align_up(o + nb * P->fs_parts * 256 * kFsSlab * sizeof(float2));
   P->ws_bytes = o;
 }
 
@@ -391,6 +404,7 @@ extern "C" holo_status holo_plan_create(const holo_geom* geom, holo_plan** out) 
     P->off_fsdinv = t;  t = align_up(t + P->fs_dinv.size() * sizeof(float));
     P->off_fssorted = t; t = align_up(t + P->fs_sorted.size() * sizeof(int));
     P->off_fsbins = t;  t = align_up(t + P->fs_bins.size() * sizeof(int));
+    P->off_fsitems = t; t = align_up(t + P->fs_items.size() * sizeof(FsItem));
     P->table_bytes = t + 256;
   } catch (const std::bad_alloc&) {
     delete P;
@@ -530,6 +544,7 @@ holo_status ensure_tables(holo_plan* P) {
   if (e == hipSuccess) e = put(P->off_fsdinv, P->fs_dinv.data(), P->fs_dinv.size() * sizeof(float));
   if (e == hipSuccess) e = put(P->off_fssorted, P->fs_sorted.data(), P->fs_sorted.size() * sizeof(int));
   if (e == hipSuccess) e = put(P->off_fsbins, P->fs_bins.data(), P->fs_bins.size() * sizeof(int));
+  if (e == hipSuccess) e = put(P->off_fsitems, P->fs_items.data(), P->fs_items.size() * sizeof(FsItem));
   if (e != hipSuccess) {
     (void)hipFree(d);
     return hip_fail(e, "uploading plan tables");
@@ -692,10 +707,14 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     fa.ang = d_ang;
     fa.sorted_k = (const int*)(tb + P->off_fssorted);
     fa.bin_first = (const int*)(tb + P->off_fsbins);
-    for (int z0 = 0; z0 < H; z0 += P->fs_slab) {
-      const int nz = std::min(P->fs_slab, H - z0);
+    fa.depth = P->fs_slab;                  // divides H
+    fa.n_items = (int)P->fs_items.size();
+    fa.n_parts = P->fs_parts;
+    fa.items = (const FsItem*)(tb + P->off_fsitems);
+    for (int z0 = 0; z0 < H; z0 += P->fs_slab * P->fs_batch) {
+      const int ns = std::min(P->fs_batch, (H - z0) / P->fs_slab);
       HOLO_HIP(timed(P, HOLO_K_RADON_FWD, st, [&] {
-        return launch_fs_forward_slab(g, fa, u + (size_t)z0 * W * W, fsG, S, z0, nz, st);
+        return launch_fs_forward(g, fa, u + (size_t)z0 * W * W, fsG, S, z0, ns, st);
       }));
     }
   } else {
@@ -869,10 +888,11 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     if (ovl) HOLO_HIP(hipEventRecord(ev_frames[ci & 1], st));
   }
   if (want_gu && fs) {
-    for (int z0 = 0; z0 < H; z0 += P->fs_slab) {
-      const int nz = std::min(P->fs_slab, H - z0);
+    float2* fsP = (float2*)(wsb + P->off_fsP);
+    for (int z0 = 0; z0 < H; z0 += P->fs_slab * P->fs_batch) {
+      const int ns = std::min(P->fs_batch, (H - z0) / P->fs_slab);
       HOLO_HIP(timed(P, HOLO_K_RADON_ADJ, st, [&] {
-        return launch_fs_adjoint_slab(g, fa, S, fsA, fsG, gu + (size_t)z0 * W * W, z0, nz, st);
+        return launch_fs_adjoint(g, fa, S, fsA, fsG, fsP, gu + (size_t)z0 * W * W, z0, ns, st);
       }));
     }
   } else if (want_gu) {

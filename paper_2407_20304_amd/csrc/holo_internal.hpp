@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 namespace holo {
 
@@ -56,8 +57,17 @@ struct DevGeom {
 constexpr int kFsWidth = 8;
 constexpr int kFsSlab = 8;
 constexpr int kFsBins = 4096;
+// One workgroup of the transpose's spread: a 16 x 16 tile of the grid, or
+// share `part` of `parts` of a tile that many lines meet (partial grid
+// `slot`, the parts of a tile in consecutive slots).
+struct FsItem {
+  int tile, part, parts, slot;
+};
 struct FsArgs {
   int K, k0;                 // the call's angles: plan angles k0 .. k0 + K - 1
+  int depth;                 // slices per slab (at most kFsSlab)
+  int n_items, n_parts;      // spread items; partial grids per slab
+  const FsItem* items;       // shared tiles first
   int n_angles;              // plan angles
   float beta;                // kernel shape exp(beta (sqrt(1 - (2x/KW)^2) - 1))
   const float* dinv;         // [W] 1 / (Fourier transform of the kernel) at x - W/2
@@ -144,16 +154,18 @@ bool pad_size_supported(int n);
 int pad_col_tiles(int H, int W);  // column tiles per frame of the padded column pass
 hipError_t launch_rows_pad(const DevGeom& g, const PadJob& jb, hipStream_t st);
 hipError_t launch_cols_pad(const DevGeom& g, const PadJob& jb, double* Fpart, hipStream_t st);
-// Fourier-slice forward of slices z0 .. z0 + nz - 1 (nz <= kFsSlab): psi of
-// every angle of the call into S[k][z][kAdjPad + s]; and its transpose from
-// h in S into g_u of those slices.  G: kFsSlab grids of (2W)^2; A:
-// kFsSlab * K * (W + 2) polar samples.
+// Fourier-slice forward of nslab slabs of f.depth slices from z0 on (u: the
+// first slab's volume): psi of every angle of the call into
+// S[k][z][kAdjPad + s]; and its transpose from h in S into g_u of those
+// slices.  Per slab, G: kFsSlab grids of (2W)^2; A: kFsSlab * n_angles *
+// (W + 1) polar samples; Part: n_parts partial tiles (256 points of kFsSlab).
 bool fs_size_supported(int W);
-hipError_t launch_fs_forward_slab(const DevGeom& g, const FsArgs& f, const float2* u_slab,
-                                  float2* G, float2* S, int z0, int nz, hipStream_t st);
-hipError_t launch_fs_adjoint_slab(const DevGeom& g, const FsArgs& f, const float2* S,
-                                  float2* A, float2* G, float2* gu_slab, int z0, int nz,
-                                  hipStream_t st);
+void fs_build_items(int W, int n_angles, std::vector<FsItem>& items, int& n_parts);
+hipError_t launch_fs_forward(const DevGeom& g, const FsArgs& f, const float2* u, float2* G,
+                             float2* S, int z0, int nslab, hipStream_t st);
+hipError_t launch_fs_adjoint(const DevGeom& g, const FsArgs& f, const float2* S, float2* A,
+                             float2* G, float2* Part, float2* gu, int z0, int nslab,
+                             hipStream_t st);
 hipError_t launch_copy_rows(const float2* src, size_t src_pitch, float2* dst, size_t rows,
                             int W, hipStream_t st);
 hipError_t launch_frames_x(const DevGeom& g, const float2* psi, const float2* Q, float2* X,

@@ -912,11 +912,19 @@ __global__ __launch_bounds__(kThreads) void k_reduce_sum(const double* __restric
 // Solver vector operations (complex64 vectors, double-precision products)
 // ---------------------------------------------------------------------------
 
-// Workgroup b sums Re(conj(a) b) over [b per, min(n, (b + 1) per)).
-__global__ __launch_bounds__(kThreads) void k_dot_re(const float2* __restrict__ a,
-                                                     const float2* __restrict__ b, size_t n,
-                                                     size_t per, double* __restrict__ parts) {
-  const size_t lo = (size_t)blockIdx.x * per, hi = min(n, lo + per);
+// Workgroup b sums Re(conj(a) b) over its share of the first (b < g1) or the
+// second pair of vectors.
+__global__ __launch_bounds__(kThreads) void k_dot_re(const float2* __restrict__ a1,
+                                                     const float2* __restrict__ b1, size_t n1,
+                                                     size_t per1, unsigned g1,
+                                                     const float2* __restrict__ a2,
+                                                     const float2* __restrict__ b2, size_t n2,
+                                                     size_t per2, double* __restrict__ parts) {
+  const bool one = blockIdx.x < g1;
+  const float2* a = one ? a1 : a2;
+  const float2* b = one ? b1 : b2;
+  const size_t per = one ? per1 : per2;
+  const size_t lo = (size_t)(one ? blockIdx.x : blockIdx.x - g1) * per, hi = min(one ? n1 : n2, lo + per);
   double acc = 0.0;
   for (size_t i = lo + threadIdx.x; i < hi; i += kThreads) {
     const float2 x = a[i], y = b[i];
@@ -1234,16 +1242,16 @@ hipError_t launch_sum_frames(const float2* G, int nd, const float2* extra, float
 hipError_t launch_dot_re(const float2* a1, const float2* b1, size_t n1, const float2* a2,
                          const float2* b2, size_t n2, double* parts, double* scratch, double* out,
                          hipStream_t st) {
-  // fixed partitions of both parts, then the two-stage sum of the partials
+  // fixed partitions of both parts in one launch, then the sum of the
+  // partials; 4096 elements per workgroup up to kDotParts / 2 of them (with
+  // 65536 the 2e6 elements of a 128^3 volume kept 32 workgroups busy for 47 us)
   auto groups = [](size_t n) {
-    return std::max<size_t>(1, std::min<size_t>(kDotParts / 2, (n + 65535) / 65536));
+    return std::max<size_t>(1, std::min<size_t>(kDotParts / 2, (n + 4095) / 4096));
   };
   const size_t g1 = groups(n1), g2 = groups(n2);
-  k_dot_re<<<(unsigned)g1, kThreads, 0, st>>>(a1, b1, n1, (n1 + g1 - 1) / g1, parts);
+  k_dot_re<<<(unsigned)(g1 + g2), kThreads, 0, st>>>(a1, b1, n1, (n1 + g1 - 1) / g1, (unsigned)g1, a2,
+                                                     b2, n2, (n2 + g2 - 1) / g2, parts);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_dot_re<<<(unsigned)g2, kThreads, 0, st>>>(a2, b2, n2, (n2 + g2 - 1) / g2, parts + g1);
-  e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_reduce_sum(parts, g1 + g2, scratch, out, st);
 }
