@@ -108,7 +108,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   constexpr int C4 = ZT / 2;                        // float4 per staged column
   static_assert(ZT == 64 && (NB == 16 || NB == 8) && LPW == 4 && kThreads == 256, "tiling");
   __shared__ float4 tile4[NBUF * ROWF2 / 2];
-  __shared__ short s_xl[kMaxW];
+  __shared__ unsigned short s_win[kMaxW];           // 16 (xl + 64) + pairs of columns - 1
+  __shared__ int s_first, s_last;                   // rows whose window meets the volume
   const int W = g.W, H = g.H;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int pz = lane & 15, bg = lane >> 4;
@@ -138,48 +139,98 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   const float span = (float)(BPT - 1) * Bf;
   const float rel_lo = fmaxf(0.0f, -span), rel_hi = (float)(SEG - 1) - fmaxf(0.0f, span) - 0.01f;
 
-  // window start of every row: lowest tap over the group's angles and the
-  // block's end bins, minus one column of margin for rounding
-  for (int r = threadIdx.x; r < W; r += kThreads) {
-    double mn = 1e300;
-    for (int a = 0; a < na; ++a) {
-      const double* ap = ang + (size_t)(gf + a) * kAngleStride;
-      const double fr = ap[kA] + (double)r * ap[kD];
-      mn = fmin(mn, fmin(fr + (double)sb * ap[kB], fr + (double)(sb + NB - 1) * ap[kB]));
-    }
-    // a window wholly outside the volume is moved into the zero padding
-    s_xl[r] = (short)min(max((int)floor(mn) - 1, -kFwdPad), W + kFwdPad - SEG);
-  }
+  // Window of every row, over the group's angles and the block's end bins:
+  // from the lowest tap minus one column to the highest tap's right
+  // neighbour plus one, columns of margin for rounding (the grouping on the
+  // host keeps that within SEG).  Only the rows whose window meets the
+  // volume are walked: the others add zeros.  A window wholly outside the
+  // volume between two such rows is moved into the zero padding, all SEG
+  // columns of it, since the taps are clamped to them.
+  if (threadIdx.x == 0) { s_first = W; s_last = -1; }
   __syncthreads();
+  int first = W, last = -1;                         // of the wave
+  for (int r0 = 0; r0 < W; r0 += kThreads) {
+    const int r = r0 + (int)threadIdx.x;            // W is a multiple of 64
+    if (r - lane >= W) break;
+    double mn = 1e300, mx = -1e300;
+#pragma unroll
+    for (int a = 0; a < kFwdNA; ++a) {              // (unrolled: the loads go together)
+      const double* ap = ang + (size_t)(gf + min(a, na - 1)) * kAngleStride;
+      const double fr = ap[kA] + (double)r * ap[kD];
+      const double f0 = fr + (double)sb * ap[kB], f1 = fr + (double)(sb + NB - 1) * ap[kB];
+      mn = fmin(mn, fmin(f0, f1));
+      mx = fmax(mx, fmax(f0, f1));
+    }
+    const int lo = (int)floor(mn) - 1, hi = (int)floor(mx) + 2;   // columns lo .. hi
+    const int xl = min(max(lo, -kFwdPad), W + kFwdPad - SEG);
+    const int pairs = xl == lo ? min((hi - lo + 2) / 2, SEG / 2) : SEG / 2;
+    s_win[r] = (unsigned short)(16 * (xl + 64) + pairs - 1);
+    const unsigned long long in = __ballot(hi >= 0 && lo < W);
+    if (in) {
+      first = min(first, r - lane + __builtin_ctzll(in));
+      last = r - lane + 63 - __builtin_clzll(in);
+    }
+  }
+  if (lane == 0 && last >= 0) { atomicMin(&s_first, first); atomicMax(&s_last, last); }
+  __syncthreads();
+  const int y_end = __builtin_amdgcn_readfirstlane(s_last + 1);
+  const int y_beg = min(__builtin_amdgcn_readfirstlane(s_first), y_end);
 
   // The volume copies are slice-blocked and padded, vol[z / ZB][row][P + col][z % ZB].
-  // Load i of wave w moves 1 KB: lane l brings slices 2 (l % 8) and
-  // 2 (l % 8) + 1 of slice block (l / 8) % 4 of column 8 w + 2 i + l / 32,
-  // which is where the [column][slice] row layout wants them (lane l lands
-  // at byte 16 l of the load's 1 KB).
+  // A load moves one pair of columns (1 KB), pairs w, w + 4, ... of a row by
+  // wave w: lane l brings slices 2 (l % 8) and 2 (l % 8) + 1 of slice block
+  // (l / 8) % 4 of column 2 pair + l / 32, which is where the [column][slice]
+  // row layout wants them (lane l lands at byte 16 l of the load's 1 KB).
+  // With 16 pairs in every row these loads set the time (512^3 x 900 angles:
+  // 27.2 ms, 19.4 without them, 26.6 without the tap reads), so a row brings
+  // no more pairs than its taps read: 23.3 ms, and 21.6 with the rows' windows
+  // read from LDS a row before use.
   const int Wf = vol_row(W);
   const size_t plane = (size_t)W * Wf * ZB;
   const float2* vl = vol + (size_t)(z0 / ZB + ((lane >> 3) & 3)) * plane +
-                     (size_t)(kFwdPad + 8 * wave + (lane >> 5)) * ZB + 2 * (lane & 7);
+                     (size_t)(kFwdPad + 2 * wave + (lane >> 5)) * ZB + 2 * (lane & 7);
   // The loads are issued as inline assembly: the compiler does not track
   // them, so it adds no waits of its own; the loop below waits for them
   // explicitly (vector-memory counter) before the barrier that publishes a
   // row.  M0 holds the wave's LDS destination of each load.
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float4*)tile4;
-  auto issue = [&](int y) {
-    const int xl = __builtin_amdgcn_readfirstlane((int)s_xl[y]);
-    const float2* row = vl + ((size_t)y * Wf + xl) * ZB;
-    const unsigned dst = __builtin_amdgcn_readfirstlane(
-        lds0 + (unsigned)(((y % NBUF) * (ROWF2 / 2) + wave * (LPW * 64)) * 16));
-#pragma unroll
-    for (int i = 0; i < LPW; ++i)
+  const int wv = __builtin_amdgcn_readfirstlane(wave);
+  // loads of row y (its s_win entry: win) into buffer buf; returns how many
+  // this wave issued
+  auto issue = [&](int y, int win, int buf) {
+    const int xl = (win >> 4) - 64, n = ((win & 15) + 4 - wv) >> 2;
+    const float2* row = vl + ((ptrdiff_t)y * Wf + xl) * ZB;
+    const unsigned dst = lds0 + (unsigned)((buf * (ROWF2 / 2) + wv * 64) * 16);
+    auto load = [&](int i) {
       asm volatile(
           "s_mov_b32 m0, %0\n\t"
           "s_nop 0\n\t"
           "global_load_lds_dwordx4 %1, off"
           :
-          : "s"(dst + 1024u * i), "v"(row + 2 * i * ZB)
+          : "s"(dst + 4096u * i), "v"(row + 8 * i * ZB)
           : "memory", "m0");
+    };
+    if (n >= 3) {                                   // the common counts, 3 and 4
+      load(0);
+      load(1);
+      load(2);
+      if (n > 3) load(3);
+    } else {
+      if (n > 0) load(0);
+      if (n > 1) load(1);
+    }
+    return n;
+  };
+  // all but the newest n loads of this wave are complete, its LDS reads too
+  auto wait_but = [&](int n) {
+    if (n >= 3) {
+      if (n > 3) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)" ::: "memory");
+    } else {
+      if (n == 2) asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)" ::: "memory");
+      else if (n == 1) asm volatile("s_waitcnt vmcnt(1) lgkmcnt(0)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    }
   };
 
   // accumulators: [bin][slice e] with slice 32 (e / 2) + 2 pz + e % 2
@@ -190,24 +241,30 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
 #pragma unroll
     for (int e = 0; e < 4; ++e) { ax[b][e] = ay[b][e] = 0.f; ox[b][e] = oy[b][e] = 0.0; }
 
-  issue(0);
-  if (W > 1) issue(1);
-  for (int y = 0; y < W; ++y) {
+  auto win_of = [&](int y) {
+    return __builtin_amdgcn_readfirstlane((int)s_win[min(y, W - 1)]);
+  };
+  // windows of rows y, y + 1 and y + 2 (read from LDS a row before use)
+  int win0 = win_of(y_beg), win1 = win_of(y_beg + 1), win2 = win_of(y_beg + 2);
+  int cur = 0, fly = 0;                             // buffer of row y; loads of row y + 1
+  if (y_beg < y_end) issue(y_beg, win0, 0);
+  if (y_beg + 1 < y_end) fly = issue(y_beg + 1, win1, 1);
+  for (int y = y_beg; y < y_end; ++y) {
     // this wave's loads of row y are complete (those of row y + 1 may be in
     // flight) and its LDS reads of row y - 1 have returned; the barrier then
     // publishes row y of every wave and retires row y - 1, whose buffer the
     // loads of row y + 2 reuse
-    if (y + 1 < W) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPW) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    wait_but(fly);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (y + 2 < W) issue(y + 2);
+    fly = y + 2 < y_end ? issue(y + 2, win2, cur == 0 ? 2 : cur - 1) : 0;
+    const int win3 = (int)s_win[min(y + 3, W - 1)];
     if (active) {
       // tap position of the thread's first bin relative to the window, in
       // double precision; the other bins add b B (< 4 sqrt(2))
-      float rel = (float)(fA + (double)y * D - (double)s_xl[y]);
+      float rel = (float)(fA + (double)y * D - (double)((win0 >> 4) - 64));
       rel = fminf(fmaxf(rel, rel_lo), rel_hi);
-      int tb = (y % NBUF) * (ROWF2 / 2) + pz;
+      int tb = cur * (ROWF2 / 2) + pz;
       asm volatile("" : "+v"(tb));                     // one base register per row
       const float4* tr = tile4 + tb;
       // software pipeline: the taps of bin b + 1 are requested before bin b
@@ -247,6 +304,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
           }
       }
     }
+    cur = cur == NBUF - 1 ? 0 : cur + 1;
+    win0 = win1;
+    win1 = win2;
+    win2 = __builtin_amdgcn_readfirstlane(win3);
   }
   if (!active) return;
   const double scale = aw[kScale];
@@ -627,7 +688,13 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
 hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uTb, float2* psi,
                             const double* ang, const int2* groups, int g0, int ngroups, int c0,
                             int c1, int nb, hipStream_t st) {
-  const unsigned n = (unsigned)(g.W / nb) * (unsigned)(g.H / kFwdZT) * (unsigned)ngroups;
+  const unsigned n16 = (unsigned)(g.W / kFwdNB) * (unsigned)(g.H / kFwdZT) * (unsigned)ngroups;
+  // Grids of fewer than two 16-bin workgroups per CU take 8-bin ones (the same
+  // groups; the windows are narrower): twice as many, each with half the work
+  // between a row's barriers.  96 workgroups of 16 bins (64 px, 90 angles)
+  // 41.3 -> 35.4 us, 240 (128 px) 74.8 -> 68.6 us, but 704 (256 px) 256 -> 325.
+  if (nb == kFwdNB && n16 < 512) nb = kFwdNB / 2;
+  const unsigned n = n16 * (unsigned)(kFwdNB / nb);
   if (nb == kFwdNB)
     k_radon_fwd<kFwdNB><<<n, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0, c1);
   else if (nb == kFwdNB / 2)
