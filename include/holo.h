@@ -91,7 +91,8 @@ typedef struct {
   double kappa;            /* 2 pi Delta / lambda: phase per unit u per voxel */
   const float* shift;      /* [n_angles][n_dist][2] = (t_y, t_x) sample
                               shifts in pixels (Eq. 9), or NULL for none   */
-  int32_t chunk;           /* angles per chunk of the frame stages; 0 = 64  */
+  int32_t chunk;           /* angles per chunk of the frame stages; 0 = 64
+                              (see holo_plan_set_chunk)                     */
 } holo_geom;
 
 typedef struct holo_plan holo_plan;
@@ -112,14 +113,16 @@ holo_status holo_workspace_bytes(const holo_plan* plan, size_t* bytes);
  * linear interpolation on the periodic H x W grid (so S_s commutes with the
  * propagators and the kernels shift Q_j = D_{rho_probe_j} q directly).
  * `shifts` is host memory [n_angles][n_dist][2], copied; NULL removes the
- * shifts.  Setting shifts grows the workspace by chunk * n_dist frames
+ * shifts.  Setting shifts grows the workspace by the frames of a chunk
  * (query holo_workspace_bytes again).  Errors: INVALID_ARGUMENT (NULL plan,
  * non-finite shift).  Host-only; the device copy is refreshed by the next
  * compute call. */
 holo_status holo_plan_set_probe_shifts(holo_plan* plan, const float* shifts);
 
 /* Angles per chunk (the frames of one chunk are formed, back-propagated and
- * dropped before the next; the workspace grows with it).  set_chunk changes
+ * dropped before the next; the workspace grows with it).  Chunks of 32 angles
+ * or more run several at a time while the frames of all their planes stay
+ * within 128 MB, and the workspace is sized for that.  set_chunk changes
  * the plan's workspace size (query holo_workspace_bytes again); chunks below
  * the plan's largest forward angle group (at most 4 angles) are rejected
  * with INVALID_ARGUMENT; values above n_angles are clamped.  Host-only. */

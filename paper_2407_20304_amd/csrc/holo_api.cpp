@@ -45,7 +45,7 @@ holo_status set_last_error(holo_status st, const std::string& msg) { return fail
 }  // namespace holo
 
 struct holo_plan {
-  int H = 0, W = 0, n_angles = 0, nd = 0, chunk = 64;
+  int H = 0, W = 0, n_angles = 0, nd = 0, chunk = 64, run_chunk = 64;
   int functional = HOLO_FUNCTIONAL_AMPLITUDE;
   int max_group = 1;                        // largest forward angle group
   double m0 = 0, fresnel0 = 0, kappa = 0;
@@ -239,7 +239,19 @@ static void layout_workspace(holo_plan* P) {
   const size_t fr = (size_t)P->H * P->W * sizeof(float2);
   size_t o = 0;
   P->off_Q = o;   o = align_up(o + fr * P->nd);
-  P->c_split = pass_c_split(P->H, P->W, P->nd, P->chunk);
+  // Angles that go through the stages together: the plan's chunk, or as many
+  // whole chunks of at least 32 angles as keep the frames under 128 MB.  A
+  // 64-angle chunk of small frames leaves the chip half empty in every launch:
+  // at 128 px and 180 angles the ray sums took 3 launches of 69 us, and take
+  // one of 97; a five-iteration solve 4.07 -> 3.05 ms.  A caller who asks for
+  // less than 32 angles wants little memory and gets that.
+  P->run_chunk = P->chunk;
+  if (P->chunk >= 32)
+    P->run_chunk = (int)std::min<size_t>(
+        P->n_angles,
+        P->chunk * std::max<size_t>(1, ((size_t)1 << 27) / (fr * P->nd * P->chunk)));
+  const int chunk = P->run_chunk;
+  P->c_split = pass_c_split(P->H, P->W, P->nd, chunk);
   P->off_G = o;   o = align_up(o + fr * P->nd * P->c_split);
   P->off_P = o;   o = align_up(o + fr);
   // z-blocked copies of the volume read by the ray sums (one per walk
@@ -249,11 +261,11 @@ static void layout_workspace(holo_plan* P) {
                         ? 0 : (size_t)P->H * P->W * vol_row(P->W) * sizeof(float2);
   P->off_ub = o;  o = align_up(o + vb);
   P->off_uTb = o; o = align_up(o + (P->any_xwalk ? vb : 0));
-  P->off_psi = o; o = align_up(o + fr * P->chunk);
+  P->off_psi = o; o = align_up(o + fr * chunk);
   // the second psi buffer of the overlapped forward (Joseph's ray sums only)
   const bool two_psi = P->overlap && P->projector == HOLO_PROJECTOR_JOSEPH;
-  P->off_psi2 = o; o = align_up(o + (two_psi ? fr * P->chunk : 0));
-  P->off_X = o;   o = align_up(o + fr * P->chunk * P->nd);
+  P->off_psi2 = o; o = align_up(o + (two_psi ? fr * chunk : 0));
+  P->off_X = o;   o = align_up(o + fr * chunk * P->nd);
   // sinogram rows carry kAdjPad zero bins on each side
   P->off_S = o;   o = align_up(o + (size_t)P->H * sino_row(P->W) * sizeof(float2) * P->n_angles);
   // cost slots: the reference term's column tiles, then every frame's; sized
@@ -266,7 +278,7 @@ static void layout_workspace(holo_plan* P) {
   // cost partials, then the reduction's stage-one sums
   P->off_F = o;   o = align_up(o + (P->n_fpart + kReduceParts) * sizeof(double));
   // with probe shifts: conj(phi) w of every frame of a chunk
-  P->off_Pbuf = o; o = align_up(o + (P->pshift.empty() ? 0 : fr * P->chunk * P->nd));
+  P->off_Pbuf = o; o = align_up(o + (P->pshift.empty() ? 0 : fr * chunk * P->nd));
   // largest magnitude of every slice of the sinogram
   P->off_smax = o; o = align_up(o + (size_t)P->H * sizeof(unsigned));
   // Fourier-slice projector: the grids of one slab and its polar samples
@@ -727,17 +739,17 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
   const bool frames_back = want_gq || want_gu;
   const int2* d_groups = (const int2*)((const char*)P->d_tables + P->off_groups);
   // Chunks [c0, c1): whole ray-sum groups (clipped to [k0, k1)), at most
-  // `chunk` angles.
+  // `run_chunk` angles.
   std::vector<int2> chunks;
   for (int c0 = k0, c1 = k0; c0 < k1; c0 = c1) {
     c1 = c0;
     while (c1 < k1) {
       const int2 gr = P->groups[P->group_of[c1]];
       const int end = std::min(gr.x + gr.y, k1);
-      if (end - c0 > P->chunk) break;
+      if (end - c0 > P->run_chunk) break;
       c1 = end;
     }
-    if (c1 == c0) c1 = std::min(c0 + P->chunk, k1);
+    if (c1 == c0) c1 = std::min(c0 + P->run_chunk, k1);
     chunks.push_back(make_int2(c0, c1));
   }
   // With the overlap on, chunk i + 1's forward runs on the side stream
