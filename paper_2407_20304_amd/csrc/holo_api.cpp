@@ -909,7 +909,9 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     }
   } else if (want_gu) {
     HOLO_HIP(timed(P, HOLO_K_RADON_ADJ, st, [&] {
-      return launch_radon_adj(g, S, gu, d_ang, k0, k1 - k0, g.smax, st);
+      // (X: the frames of the last chunk are no longer needed)
+      return launch_radon_adj(g, S, gu, d_ang, k0, k1 - k0, g.smax, X,
+                              (size_t)P->run_chunk * nd / W, st);
     }));
   }
   if (want_gq) {

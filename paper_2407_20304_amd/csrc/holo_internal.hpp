@@ -197,8 +197,10 @@ hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uT
 // Transpose of the ray sums over angles k0 .. k0 + K - 1: S holds their
 // sinogram in pass D's blocked layout (overwritten by its split form), ang
 // the plan's whole angle table, smax the slices' largest magnitudes.
+// tmp: room for tmp_volumes volumes of partial sums (0: none).
 hipError_t launch_radon_adj(const DevGeom& g, float2* S, float2* gu, const double* ang, int k0,
-                            int K, const unsigned* smax, hipStream_t st);
+                            int K, const unsigned* smax, float2* tmp, size_t tmp_volumes,
+                            hipStream_t st);
 // (clears smax)
 hipError_t launch_block_volume(const DevGeom& g, const float2* u, float2* ub, float2* uTb,
                                unsigned* smax, hipStream_t st);

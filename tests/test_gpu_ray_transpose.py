@@ -56,3 +56,18 @@ def test_scaled_sinograms():
     for e in (-60, 40):
         assert_close(_adj(p, (w * np.float32(2.0 ** e)), 0, 5) * 2.0 ** -e, ref, "scaled by 2^%d" % e, tol=1e-6,
                      max_tol=1e-6)
+
+
+@pytest.mark.parametrize("H,W,n,nd", [
+    (64, 64, 31, 4),       # 8 groups of 4 angles, the last one short: 2 shares
+    (64, 64, 77, 8),       # 20 groups: 5 shares
+    (128, 128, 37, 4),     # 128 tiles: 2 shares
+    (64, 128, 37, 4),      # 64 tiles, 10 groups: 2 shares
+])
+def test_shared_angles(H, W, n, nd):
+    """Volumes of few tiles share their angles out and add the parts up."""
+    theta = np.linspace(-0.3, 2 * np.pi, n)
+    p = make_problem(H, W, n, config=48, chunk=32, theta=theta, mag_rel=tuple(1 + 0.05 * np.arange(nd)))
+    w = _w(p, n, 9)
+    gu, _ = O.adjoint(c128(p.u), c128(p.q), c128(w), p.geom)
+    assert_close(_adj(p, w, 0, n), gu, "g_u")
