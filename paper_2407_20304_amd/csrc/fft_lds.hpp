@@ -410,4 +410,20 @@ __device__ __forceinline__ void fft_e(float2 (&e)[N / TL], float2* line, const f
   }
 }
 
+// Twiddles of an N-point transform into padded LDS by a workgroup of T
+// threads.  All loads first: a plain strided loop is compiled to one load and
+// one wait per element.
+template <int N, int T>
+__device__ __forceinline__ void load_twiddles(float2* s_tw, const float2* __restrict__ tw) {
+  constexpr int C = (N + T - 1) / T;
+  const int t = threadIdx.x;
+  float2 w[C];
+#pragma unroll
+  for (int e = 0; e < C; ++e)
+    if (N % T == 0 || t + e * T < N) w[e] = tw[t + e * T];
+#pragma unroll
+  for (int e = 0; e < C; ++e)
+    if (N % T == 0 || t + e * T < N) s_tw[fpi(t + e * T)] = w[e];
+}
+
 }  // namespace holo

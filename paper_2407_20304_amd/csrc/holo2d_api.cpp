@@ -19,6 +19,8 @@ holo_status set_last_error(holo_status st, const std::string& msg);
 
 namespace {
 
+constexpr int kProbeGroups = 512;
+
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct ItemList {
@@ -33,6 +35,7 @@ struct holo2d_plan {
   int functional = 0;                     // holo_functional
   double m0 = 0, fresnel0 = 0;
   std::vector<double> mag;
+  unsigned unit = 0;                      // planes of magnification 1 (bit j)
   std::vector<int> sizes;
   std::vector<long long> off;
   long long total = 0;
@@ -124,6 +127,8 @@ extern "C" holo_status holo2d_plan_create(int32_t n_inst, const int32_t* sizes, 
     P->m0 = m0;
     P->fresnel0 = fresnel0;
     P->mag.assign(mag_rel, mag_rel + n_dist);
+    for (int j = 0; j < n_dist; ++j)
+      if (P->mag[j] == 1.0) P->unit |= 1u << j;
     P->sizes.assign(sizes, sizes + n_inst);
     P->off.resize(n_inst);
     for (int i = 0; i < n_inst; ++i) {
@@ -171,31 +176,44 @@ extern "C" holo_status holo2d_plan_create(int32_t n_inst, const int32_t* sizes, 
       slots += per * (n_dist + 1);
     }
     P->n_slots = slots;
+    // Jobs per workgroup of the probe rows: as many as leave kProbeGroups
+    // workgroups.  Small batches need the workgroups more than they save on
+    // transforms (6 problems, 0.3 Mpx: 123 us a call either way; 12 problems,
+    // 1 Mpx: 210 us with 512 and 217 with 2048; 24: 351 and 361).
+    long long wgs = 0;
+    for (int i = 0; i < n_inst; ++i) wgs += P->sizes[i] / b2_rows_per_wg(P->sizes[i]);
+    const int share = (int)std::max<long long>(1, std::min<long long>(n_dist + 1, wgs * (n_dist + 1) / kProbeGroups));
     for (int i : order) {
       const int n = P->sizes[i];
       const int lpw = b2_rows_per_wg(n), tc = b2_cols_per_wg(n);
       // job n_dist of the probe and pass-C rows is the reference term
       for (int j = 0; j <= n_dist; ++j)
         for (int z = 0; z < n; z += lpw) {
-          P->rows_probe.items.push_back({i, j, z, 0});
           P->rows_cgq.items.push_back({i, j, z, 0});
-          if (j < n_dist) {
-            P->rows_probe_noref.items.push_back({i, j, z, 0});
-            P->rows_nd.items.push_back({i, j, z, 0});
-          }
+          if (j < n_dist) P->rows_nd.items.push_back({i, j, z, 0});
         }
+      // probe rows: up to `share` jobs to a workgroup, which transforms the
+      // row of q once for them
+      for (int j0 = 0; j0 <= n_dist; j0 += share) {
+        const int j1 = std::min(j0 + share, n_dist + 1), jn = std::min(j1, n_dist);
+        for (int z = 0; z < n; z += lpw) {
+          P->rows_probe.items.push_back({i, j0, z, j1});
+          if (j0 < jn) P->rows_probe_noref.items.push_back({i, j0, z, jn});
+        }
+      }
       for (int j = 0; j <= n_dist; ++j)
         for (int s = 0; s < n; s += tc) {
           // cost slots: plane j's column tiles, then the reference's
           const int slot = slot_base[i] + (j < n_dist ? j : n_dist) * (n / tc) + s / tc;
-          P->cols_probe.items.push_back({i, j, s, slot});
+          if (!((P->unit >> j) & 1)) P->cols_probe.items.push_back({i, j, s, slot});
           if (j < n_dist) {
-            P->cols_probe_noref.items.push_back({i, j, s, 0});
+            if (!((P->unit >> j) & 1)) P->cols_probe_noref.items.push_back({i, j, s, 0});
             P->cols_nd.items.push_back({i, j, s, slot});
           }
         }
       for (int s = 0; s < n; s += b2_gq_per_wg(n)) P->cols_gq.items.push_back({i, 0, s, 0});
-      for (int p = 0; p < n * n; p += 256) P->gather.items.push_back({i, 0, p, 0});
+      // (supported sizes are multiples of 64)
+      for (int b = 0; b < n / 64 * (n / kGatherRows); ++b) P->gather.items.push_back({i, 0, b, 0});
     }
     // device table layout
     size_t t = 0;
@@ -353,6 +371,8 @@ holo_status b2_launch(holo2d_plan* P, B2Run run, const char* tb, char* w, const 
   A.nd = P->nd;
   A.functional = P->functional == HOLO_FUNCTIONAL_INTENSITY ? 1 : 0;
   A.max_n = P->dsizes.back();
+  A.unit = P->unit;
+  A.ident = conv ? 0 : P->unit;   // rho_probe_j = 0
   for (int j = 0; j < P->nd; ++j) A.mag[j] = P->mag[j];
   A.inst = (const B2Inst*)(tb + P->off_inst);
   A.psi = (const float2*)psi;
@@ -381,7 +401,7 @@ holo_status b2_launch(holo2d_plan* P, B2Run run, const char* tb, char* w, const 
   } else {
     A.mode = kB2RowsProbe;
     const ItemList& rp = want_ref ? P->rows_probe : P->rows_probe_noref;
-    B2_HIP(launch_b2_rows(A, items(rp), (int)rp.items.size(), st));
+    B2_HIP(launch_b2_probe_rows(A, items(rp), (int)rp.items.size(), st));
     A.mode = kB2ColsProbe;
     const ItemList& cp = want_ref ? P->cols_probe : P->cols_probe_noref;
     B2_HIP(launch_b2_cols(A, items(cp), (int)cp.items.size(), st));
@@ -402,10 +422,10 @@ holo_status b2_launch(holo2d_plan* P, B2Run run, const char* tb, char* w, const 
       A.mode = kB2ColsGqSum;
       B2_HIP(launch_b2_gq_sum(A, items(P->cols_gq), (int)P->cols_gq.items.size(), st));
     }
-    if (g_psi) B2_HIP(launch_b2_gather(A, items(P->gather), (int)P->gather.items.size(), st));
   }
-  if (F && run != kB2Fwd)
-    B2_HIP(launch_b2_reduce(A.Fpart, (const int2*)(tb + P->off_ranges), P->n_inst, F, st));
+  const bool want_F = F && run != kB2Fwd;
+  B2_HIP(launch_b2_gather(A, items(P->gather), grad && g_psi ? (int)P->gather.items.size() : 0,
+                          (const int2*)(tb + P->off_ranges), want_F ? P->n_inst : 0, F, st));
   return HOLO_OK;
 }
 

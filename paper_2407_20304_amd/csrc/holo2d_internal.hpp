@@ -22,12 +22,15 @@ struct B2Inst {
   const B2AdjTap* adj;     // [nd][n] transposed demagnification taps of an axis
 };
 
+// Work item of one workgroup: an instance, a plane or job, the first line (or
+// block of the gather) and the cost slot.  Probe rows: jobs [job, slot).
 struct B2Item {
   int inst, job, line0, slot;
 };
 
 // Passes of the batched gradient (one launch each):
 //   kB2RowsProbe  rows of D_{rho_probe_j} q (jobs < nd) and of D_1 q (job nd)
+//                 from one transform of each row of q
 //   kB2ColsProbe  their columns; job nd: reference residual and cost, then
 //                 (want_gq) the columns of D_{-1} on it
 //   kB2RowsA      pass A rows;  kB2ColsB  pass B columns
@@ -47,6 +50,8 @@ struct B2Args {
   int want_gq;             // the probe gradient is wanted (and the reference term with it)
   int functional;          // 0: amplitude (F2), 1: intensity (F1)
   int max_n;               // largest instance size of the batch
+  unsigned unit;           // planes of magnification 1: B_j is the identity
+  unsigned ident;          // planes whose Q_j is q itself (D_{rho_probe_j} = 1)
   double mag[8];
   const B2Inst* inst;
   const float2* psi;
@@ -62,16 +67,20 @@ struct B2Args {
   double* Fpart;
 };
 
+constexpr int kGatherRows = 8;   // rows (of 64 columns) of one gather item
+
 int b2_rows_per_wg(int n);
 int b2_cols_per_wg(int n);
 int b2_gq_per_wg(int n);
 bool b2_size_supported(int n);
 
+hipError_t launch_b2_probe_rows(const B2Args& A, const B2Item* items, int n, hipStream_t st);
 hipError_t launch_b2_rows(const B2Args& A, const B2Item* items, int n, hipStream_t st);
 hipError_t launch_b2_cols(const B2Args& A, const B2Item* items, int n, hipStream_t st);
 hipError_t launch_b2_gq_sum(const B2Args& A, const B2Item* items, int n, hipStream_t st);
-hipError_t launch_b2_gather(const B2Args& A, const B2Item* items, int n, hipStream_t st);
-hipError_t launch_b2_reduce(const double* parts, const int2* ranges, int n_inst, double* F,
-                            hipStream_t st);
+// The n gather items (0: no g_psi) and the costs of n_inst instances (0: no
+// F) in one launch.
+hipError_t launch_b2_gather(const B2Args& A, const B2Item* items, int n, const int2* ranges,
+                            int n_inst, double* F, hipStream_t st);
 
 }  // namespace holo
