@@ -40,13 +40,17 @@ __host__ __device__ constexpr int b_col_pitch(int n, int tc) {
   return (fft_line_len(n) - 32 / tc + 64 / tc - 1) / (64 / tc) * (64 / tc) + 32 / tc;
 }
 // LDS of one column workgroup of size n: twiddles plus the tile.
-__host__ __device__ constexpr int b_cols_lds(int n) { return fft_line_len(n) + b_cols_tc(n) * b_col_pitch(n, b_cols_tc(n)); }
+__host__ __device__ constexpr int b_cols_lds(int n) {
+  return fft_line_len(n) + b_cols_tc(n) * b_col_pitch(n, b_cols_tc(n));
+}
 
 // The probe-gradient column pass keeps every plane's spectrum sum in
 // registers next to the plane being transformed: 4 columns per workgroup
 // (64 threads per column) keep that to 2 x n / 64 elements per thread.
 __host__ __device__ constexpr int b_gq_tc(int) { return 4; }
-__host__ __device__ constexpr int b_gq_lds(int n) { return fft_line_len(n) + b_gq_tc(n) * b_col_pitch(n, b_gq_tc(n)); }
+__host__ __device__ constexpr int b_gq_lds(int n) {
+  return fft_line_len(n) + b_gq_tc(n) * b_col_pitch(n, b_gq_tc(n));
+}
 
 int b2_rows_per_wg(int n) { return b_rows_lpw(n); }
 int b2_cols_per_wg(int n) { return b_cols_tc(n); }
@@ -435,7 +439,8 @@ __device__ __forceinline__ int xcd_runs(int h, int n) {
 // LDS: the host launches the small instantiation only for batches whose
 // largest instance is at most 512 px.
 template <int LDS>
-__global__ __launch_bounds__(kC2) __attribute__((amdgpu_waves_per_eu(LDS == kColLdsSmall ? 4 : 2))) void k2_cols(B2Args A, const B2Item* __restrict__ items) {
+__global__ __launch_bounds__(kC2) __attribute__((amdgpu_waves_per_eu(LDS == kColLdsSmall ? 4 : 2))) void k2_cols(
+    B2Args A, const B2Item* __restrict__ items) {
   __shared__ float2 lds[LDS];
   const B2Item it = items[xcd_runs(blockIdx.x, gridDim.x)];
   switch (A.inst[it.inst].n) {

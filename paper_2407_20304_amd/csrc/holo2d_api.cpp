@@ -182,7 +182,8 @@ extern "C" holo_status holo2d_plan_create(int32_t n_inst, const int32_t* sizes, 
     // 1 Mpx: 210 us with 512 and 217 with 2048; 24: 351 and 361).
     long long wgs = 0;
     for (int i = 0; i < n_inst; ++i) wgs += P->sizes[i] / b2_rows_per_wg(P->sizes[i]);
-    const int share = (int)std::max<long long>(1, std::min<long long>(n_dist + 1, wgs * (n_dist + 1) / kProbeGroups));
+    const int share = (int)std::max<long long>(
+        1, std::min<long long>(n_dist + 1, wgs * (n_dist + 1) / kProbeGroups));
     for (int i : order) {
       const int n = P->sizes[i];
       const int lpw = b2_rows_per_wg(n), tc = b2_cols_per_wg(n);

@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kThreads) void k_pass_a(const float2* __restrict__ 
   const int z = blockIdx.x * LPW + line;
   const int f = blockIdx.y;
   const int k = f / g.nd, j = f % g.nd;
-  for (int i = threadIdx.x; i < W; i += kThreads) s_tw[fpi(i)] = g.twW[i];
+  load_twiddles<W, kThreads>(s_tw, g.twW);
 
   double ty, tx;
   shift_of(g, k_first + k, j, ty, tx);
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kThreads, !PS && W % 3 != 0 ? 4 : 1) void k_pass_c(
   // this workgroup's share of the chunk's angles, and its slot of G
   const int per = (Kc + gridDim.z - 1) / gridDim.z;
   const int kb = blockIdx.z * per, ke = min(kb + per, Kc);
-  for (int i = threadIdx.x; i < W; i += kThreads) s_tw[fpi(i)] = g.twW[i];
+  load_twiddles<W, kThreads>(s_tw, g.twW);
   const double m = g.mag[j];
   const float2* Qrow = Q + ((size_t)j * g.H + z) * W;
   const float2* ch = g.chirpW + (size_t)chirp_det(j) * W;
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_prop(PropJobs jobs, DevGeom g
   const int lp = fpi(lt);   // padded position of the thread's first element
   const int z = blockIdx.x * LPW + line;
   const PropJob& jb = jobs.job[blockIdx.y];
-  for (int i = threadIdx.x; i < W; i += kThreads) s_tw[fpi(i)] = g.twW[i];
+  load_twiddles<W, kThreads>(s_tw, g.twW);
   const float2* in = jb.src + (size_t)z * W;
   float2* L = s_line[line];
 #pragma unroll
@@ -473,37 +473,53 @@ __global__ __launch_bounds__(kColThreads) void k_cols_prop(PropJobs jobs, double
   const int W = g.W;
   const int s0 = blockIdx.x * TC;
   const PropJob& jb = jobs.job[blockIdx.y];
-  for (int i = threadIdx.x; i < H; i += kColThreads) s_tw[fpi(i)] = g.twH[i];
-  const float2* in = jb.src + s0;
-  for (int i = threadIdx.x; i < H * TC; i += kColThreads) {
-    const int zz = i / TC, cc = i % TC;
-    s_col[cc][fpi(zz)] = in[(size_t)zz * W + cc];
-  }
+  // Tile order, loads and transforms as in k_pass_b: every load of the tile
+  // before the first wait, elements in registers around the transforms.
+  constexpr int EC = H / TLc, NPT = H * TC / kColThreads, RS = kColThreads / TC, LSTEP = RS + RS / 32;
+  static_assert(RS % 32 == 0, "padded tile steps");
+  const int z0 = threadIdx.x / TC, cc = threadIdx.x % TC;
+  const float2* in = jb.src + s0 + (size_t)z0 * W + cc;
+  float2 t[NPT], v[EC];
+#pragma unroll
+  for (int r = 0; r < NPT; ++r) t[r] = in[(size_t)r * RS * W];
+  load_twiddles<H, kColThreads>(s_tw, g.twH);
+  float2* l0 = &s_col[cc][fpi(z0)];
+#pragma unroll
+  for (int r = 0; r < NPT; ++r) l0[r * LSTEP] = t[r];
   float2* L = s_col[c];
   const float2* ch = g.chirpH + (size_t)jb.chirp * H;
   constexpr bool WL = wave_lines(TLc);
-  if constexpr (WL) __syncthreads();   // tile and s_tw
-  fft<H, TLc, false, true, WL>(L, s_tw, lt);
-  for (int zz = lt; zz < H; zz += TLc) L[fpi(zz)] = jb.conj ? cmulc(L[fpi(zz)], ch[zz]) : cmul(L[fpi(zz)], ch[zz]);
-  fft<H, TLc, true, true, WL>(L, s_tw, lt);
+  __syncthreads();   // tile and s_tw
+#pragma unroll
+  for (int e = 0; e < EC; ++e) v[e] = L[fpi(lt + e * TLc)];
+  fft_e<H, TLc, false, true, WL>(v, L, s_tw, lt);
+#pragma unroll
+  for (int e = 0; e < EC; ++e) {
+    const float2 h = ch[lt + e * TLc];
+    v[e] = jb.conj ? cmulc(v[e], h) : cmul(v[e], h);
+  }
+  fft_e<H, TLc, true, true, WL>(v, L, s_tw, lt);
+  __syncthreads();   // every column's exchange reads are done
+#pragma unroll
+  for (int e = 0; e < EC; ++e) L[fpi(lt + e * TLc)] = v[e];
+  float ar[NPT];
+  if (jb.amp) {
+    const float* a = jb.amp + s0 + (size_t)z0 * W + cc;
+#pragma unroll
+    for (int r = 0; r < NPT; ++r) ar[r] = a[(size_t)r * RS * W];
+  }
   __syncthreads();
+#pragma unroll
+  for (int r = 0; r < NPT; ++r) t[r] = l0[r * LSTEP];
   if (jb.amp) {
     double acc = 0.0;
-    const float* a = jb.amp + s0;
-    for (int i = threadIdx.x; i < H * TC; i += kColThreads) {
-      const int zz = i / TC, cc = i % TC;
-      float2 v = s_col[cc][fpi(zz)];
-      acc += residual(v, a[(size_t)zz * W + cc], g.functional);
-      s_col[cc][fpi(zz)] = v;
-    }
+#pragma unroll
+    for (int r = 0; r < NPT; ++r) acc += residual(t[r], ar[r], g.functional);
     block_sum_store<kColThreads>(acc, Fpart + (size_t)jb.fslot * gridDim.x + blockIdx.x);
-    __syncthreads();
   }
-  float2* out = jb.dst + s0;
-  for (int i = threadIdx.x; i < H * TC; i += kColThreads) {
-    const int zz = i / TC, cc = i % TC;
-    out[(size_t)zz * W + cc] = s_col[cc][fpi(zz)];
-  }
+  float2* out = jb.dst + s0 + (size_t)z0 * W + cc;
+#pragma unroll
+  for (int r = 0; r < NPT; ++r) out[(size_t)r * RS * W] = t[r];
 }
 
 // Columns of the probe gradient: g_q = sum_i D_{-rho_i} f_i over the jobs'
@@ -523,7 +539,10 @@ __global__ __launch_bounds__(kThreads) void k_cols_gq(PropJobs jobs, float2* __r
   const int c = threadIdx.x / TLc, lt = threadIdx.x % TLc;
   const int W = g.W;
   const int s0 = blockIdx.x * TC;
-  for (int i = threadIdx.x; i < H; i += kThreads) s_tw[fpi(i)] = g.twH[i];
+  load_twiddles<H, kThreads>(s_tw, g.twH);
+  constexpr int RS = kThreads / TC;    // rows between a thread's tile elements (EC of them)
+  constexpr int GL = EC > 8 && EC % 8 == 0 ? 8 : EC;
+  const int z0 = threadIdx.x / TC, cc = threadIdx.x % TC;
   float2* Lc = s_col[c];
   float2 acc[EC];
 #pragma unroll
@@ -531,9 +550,13 @@ __global__ __launch_bounds__(kThreads) void k_cols_gq(PropJobs jobs, float2* __r
   for (int n = 0; n < jobs.n; ++n) {
     const float2* in = jobs.job[n].src + s0;
     __syncthreads();                   // the previous frame's tile has been read
-    for (int i = threadIdx.x; i < H * TC; i += kThreads) {
-      const int zz = i / TC, cc = i % TC;
-      s_col[cc][fpi(zz)] = in[(size_t)zz * W + cc];
+#pragma unroll 1
+    for (int b = 0; b < EC; b += GL) {   // GL loads at a time
+      float2 t[GL];
+#pragma unroll
+      for (int e = 0; e < GL; ++e) t[e] = in[(size_t)(z0 + (b + e) * RS) * W + cc];
+#pragma unroll
+      for (int e = 0; e < GL; ++e) s_col[cc][fpi(z0 + (b + e) * RS)] = t[e];
     }
     __syncthreads();                   // tile and s_tw
     float2 v[EC];
@@ -549,10 +572,8 @@ __global__ __launch_bounds__(kThreads) void k_cols_gq(PropJobs jobs, float2* __r
 #pragma unroll
   for (int e = 0; e < EC; ++e) Lc[fpi(lt + e * TLc)] = acc[e];
   __syncthreads();
-  for (int i = threadIdx.x; i < H * TC; i += kThreads) {
-    const int zz = i / TC, cc = i % TC;
-    gq[(size_t)zz * W + s0 + cc] = s_col[cc][fpi(zz)];
-  }
+#pragma unroll 4
+  for (int e = 0; e < EC; ++e) gq[(size_t)(z0 + e * RS) * W + s0 + cc] = s_col[cc][fpi(z0 + e * RS)];
 }
 
 // ---------------------------------------------------------------------------
@@ -575,33 +596,35 @@ __global__ __launch_bounds__(kThreads) void k_rows_pad(PadJob jb, DevGeom g) {
   const int line = threadIdx.x / TL, lt = threadIdx.x % TL;
   const int z = blockIdx.x * LPW + line;
   const int f = blockIdx.y;
-  for (int i = threadIdx.x; i < N2; i += kThreads) s_tw[fpi(i)] = g.tw2W[i];
-  const float2* in = jb.src + (size_t)f * jb.src_step + (size_t)z * W;
-  float2* L = s_line[line];
+  // The elements n = lt + e TL stay in registers; those of the centre are
+  // e in [E0, E1).
+  static_assert(OFF % TL == 0 && W % TL == 0, "the centre is whole steps");
+  constexpr int E0 = OFF / TL, E1 = (OFF + W) / TL;
+  const float2* in = jb.src + (size_t)f * jb.src_step + (size_t)z * W - OFF + lt;
+  float2 v[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int n = lt + e * TL;
-    L[fpi(n)] = (n >= OFF && n < OFF + W) ? in[n - OFF] : make_float2(0.f, 0.f);
-  }
-  if constexpr (wave_lines(TL)) __syncthreads();   // s_tw
-  fft<N2, TL, false, true, wave_lines(TL)>(L, s_tw, lt);
+  for (int e = 0; e < E; ++e) v[e] = e >= E0 && e < E1 ? in[e * TL] : make_float2(0.f, 0.f);
+  load_twiddles<N2, kThreads>(s_tw, g.tw2W);
+  float2* L = s_line[line];
+  constexpr bool WL = wave_lines(TL);
+  if constexpr (WL) __syncthreads();   // s_tw
+  fft_e<N2, TL, false, true, WL>(v, L, s_tw, lt);
   const float2* ch = g.chirp2W + (size_t)(jb.chirp0 + f % jb.cmod) * N2;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int n = lt + e * TL;
-    L[fpi(n)] = jb.conj ? cmulc(L[fpi(n)], ch[n]) : cmul(L[fpi(n)], ch[n]);
+    const float2 h = ch[lt + e * TL];
+    v[e] = jb.conj ? cmulc(v[e], h) : cmul(v[e], h);
   }
-  fft<N2, TL, true, true, wave_lines(TL)>(L, s_tw, lt);
-  float2* out = jb.dst + (size_t)f * g.H * W + (size_t)z * W;
+  fft_e<N2, TL, true, true, WL>(v, L, s_tw, lt);
+  float2* out = jb.dst + (size_t)f * g.H * W + (size_t)z * W - OFF + lt;
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int n = lt + e * TL;
-    if (n >= OFF && n < OFF + W) out[n - OFF] = L[fpi(n)];
-  }
+  for (int e = E0; e < E1; ++e) out[e * TL] = v[e];
 }
 
+// (two workgroups per CU where their LDS fits twice: 192 and 512 would take
+// 130 and 134 VGPRs)
 template <int H>
-__global__ __launch_bounds__(kColThreads) void k_cols_pad(PadJob jb, double* __restrict__ Fpart,
+__global__ __launch_bounds__(kColThreads, H == 384 || H == 1024 ? 2 : 4) void k_cols_pad(PadJob jb, double* __restrict__ Fpart,
                                                           DevGeom g, int ntiles) {
   constexpr int N2 = 2 * H, TC = cols_tc(N2), TLc = kColThreads / TC;
   constexpr int OFF = H / 2;
@@ -612,48 +635,72 @@ __global__ __launch_bounds__(kColThreads) void k_cols_pad(PadJob jb, double* __r
   const int tile = blockIdx.x % ntiles, f = blockIdx.x / ntiles;
   const int s0 = tile * TC;
   const size_t HW = (size_t)H * W;
-  for (int i = threadIdx.x; i < N2; i += kColThreads) s_tw[fpi(i)] = g.tw2H[i];
-  const float2* in = jb.src + (size_t)f * jb.src_step + s0;
-  for (int i = threadIdx.x; i < N2 * TC; i += kColThreads) {
-    const int zz = i / TC, cc = i % TC;
-    s_col[cc][fpi(zz)] = (zz >= OFF && zz < OFF + H) ? in[(size_t)(zz - OFF) * W + cc]
-                                                     : make_float2(0.f, 0.f);
-  }
+  // As k_pass_b, with the tile's H rows in the centre of the lines: loads,
+  // stores and the residual touch the centre only, the elements e outside
+  // [E0, E1) start as zeros in registers.  Bound by the 512-point transforms
+  // in LDS; 256 px, 180 angles: 780 -> 573 us (and k_rows_pad 590 -> 436).
+  constexpr int EC = N2 / TLc, NPT = H * TC / kColThreads, RS = kColThreads / TC, LSTEP = RS + RS / 32;
+  constexpr int E0 = OFF / TLc, E1 = (OFF + H) / TLc;
+  static_assert(RS % 32 == 0 && OFF % 32 == 0, "padded tile steps");
+  static_assert(OFF % TLc == 0 && H % TLc == 0, "the centre is whole steps");
+  const int z0 = threadIdx.x / TC, cc = threadIdx.x % TC;
+  const size_t t0 = (size_t)z0 * W + cc;
+  const float2* in = jb.src + (size_t)f * jb.src_step + s0 + t0;
+  float2 t[NPT], v[EC];
+#pragma unroll
+  for (int r = 0; r < NPT; ++r) t[r] = in[(size_t)r * RS * W];
+  load_twiddles<N2, kColThreads>(s_tw, g.tw2H);
+  float2* l0 = &s_col[cc][fpi(z0 + OFF)];
+#pragma unroll
+  for (int r = 0; r < NPT; ++r) l0[r * LSTEP] = t[r];
   float2* L = s_col[c];
   const float2* ch = g.chirp2H + (size_t)(jb.chirp0 + f % jb.cmod) * N2;
   constexpr bool WL = wave_lines(TLc);
   const bool cj = jb.mode == 0 && jb.conj;
-  if constexpr (WL) __syncthreads();   // tile and s_tw
-  fft<N2, TLc, false, true, WL>(L, s_tw, lt);
-  for (int zz = lt; zz < N2; zz += TLc) L[fpi(zz)] = cj ? cmulc(L[fpi(zz)], ch[zz]) : cmul(L[fpi(zz)], ch[zz]);
-  fft<N2, TLc, true, true, WL>(L, s_tw, lt);
-  __syncthreads();
+  __syncthreads();   // tile and s_tw
+#pragma unroll
+  for (int e = 0; e < EC; ++e) v[e] = e >= E0 && e < E1 ? L[fpi(lt + e * TLc)] : make_float2(0.f, 0.f);
+  fft_e<N2, TLc, false, true, WL>(v, L, s_tw, lt);
+#pragma unroll
+  for (int e = 0; e < EC; ++e) {
+    const float2 h = ch[lt + e * TLc];
+    v[e] = cj ? cmulc(v[e], h) : cmul(v[e], h);
+  }
+  fft_e<N2, TLc, true, true, WL>(v, L, s_tw, lt);
   if (jb.mode != 0) {
     // residual on the kept centre; the rest is cleared before the adjoint
+    fft_sync<WL>();                    // the column's exchange reads are done
+#pragma unroll
+    for (int e = E0; e < E1; ++e) L[fpi(lt + e * TLc)] = v[e];
+    const float* a = jb.amp + (size_t)f * HW + s0 + t0;
+    float ar[NPT];
+#pragma unroll
+    for (int r = 0; r < NPT; ++r) ar[r] = a[(size_t)r * RS * W];
+    __syncthreads();
     double acc = 0.0;
-    const float* a = jb.amp + (size_t)f * HW + s0;
-    for (int i = threadIdx.x; i < N2 * TC; i += kColThreads) {
-      const int zz = i / TC, cc = i % TC;
-      float2 v = make_float2(0.f, 0.f);
-      if (zz >= OFF && zz < OFF + H) {
-        v = s_col[cc][fpi(zz)];
-        acc += residual(v, a[(size_t)(zz - OFF) * W + cc], g.functional);
-      }
-      s_col[cc][fpi(zz)] = v;
+#pragma unroll
+    for (int r = 0; r < NPT; ++r) {
+      float2 w = l0[r * LSTEP];
+      acc += residual(w, ar[r], g.functional);
+      l0[r * LSTEP] = w;
     }
+    // (its barrier also publishes the residual writes)
     block_sum_store<kColThreads>(acc, Fpart + jb.fslot0 + (size_t)f * ntiles + tile);
     if (jb.mode == 2) return;
-    if constexpr (WL) __syncthreads();
-    fft<N2, TLc, false, true, WL>(L, s_tw, lt);
-    for (int zz = lt; zz < N2; zz += TLc) L[fpi(zz)] = cmulc(L[fpi(zz)], ch[zz]);
-    fft<N2, TLc, true, true, WL>(L, s_tw, lt);
-    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EC; ++e) v[e] = e >= E0 && e < E1 ? L[fpi(lt + e * TLc)] : make_float2(0.f, 0.f);
+    fft_e<N2, TLc, false, true, WL>(v, L, s_tw, lt);
+#pragma unroll
+    for (int e = 0; e < EC; ++e) v[e] = cmulc(v[e], ch[lt + e * TLc]);
+    fft_e<N2, TLc, true, true, WL>(v, L, s_tw, lt);
   }
-  float2* out = jb.dst + (size_t)f * HW + s0;
-  for (int i = threadIdx.x; i < H * TC; i += kColThreads) {
-    const int zz = i / TC, cc = i % TC;
-    out[(size_t)zz * W + cc] = s_col[cc][fpi(zz + OFF)];
-  }
+  __syncthreads();                     // every column's exchange reads are done
+#pragma unroll
+  for (int e = E0; e < E1; ++e) L[fpi(lt + e * TLc)] = v[e];
+  __syncthreads();
+  float2* out = jb.dst + (size_t)f * HW + s0 + t0;
+#pragma unroll
+  for (int r = 0; r < NPT; ++r) out[(size_t)r * RS * W] = l0[r * LSTEP];
 }
 
 // x_kj = Q_kj phi_kj for every pixel of a chunk's frames (pass A without
