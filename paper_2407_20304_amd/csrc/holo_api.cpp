@@ -816,17 +816,13 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     }
     double* Fc = Fpart + ref_tiles + (size_t)tiles * (c0 - k0) * nd;
     if (padded) {
-      // the unfused sequence: elementwise pass A, padded rows, padded
-      // columns (with the residual and the adjoint columns), padded adjoint
-      // rows, elementwise pass C
+      // padded rows of x = Q phi, padded columns (with the residual and the
+      // adjoint columns), padded adjoint rows, elementwise pass C
       const int nf = Kc * nd;
       float2* F0 = mode == kFwd ? v_out + (size_t)(c0 - k0) * nd * HW : X;
       if (mode != kAdj) {
-        HOLO_HIP(timed(P, HOLO_K_PASS_A, st, [&] {
-          return launch_frames_x(g, psi_c, Q, F0, c0, Kc, st);
-        }));
         const PadJob rf = pj(F0, F0, hw, nf, chirp_det(0), nd, 0, 0, nullptr, 0);
-        HOLO_HIP(timed(P, HOLO_K_PASS_A, st, [&] { return launch_rows_pad(g, rf, st); }));
+        HOLO_HIP(timed(P, HOLO_K_PASS_A, st, [&] { return launch_rows_pad(g, rf, st, psi_c, Q, c0); }));
       }
       PadJob cf;
       if (mode == kFwd) {

@@ -152,7 +152,9 @@ hipError_t launch_pass_a(const DevGeom& g, const float2* psi, const float2* Q, f
 // passes A and C that surround it when the plan propagates padded.
 bool pad_size_supported(int n);
 int pad_col_tiles(int H, int W);  // column tiles per frame of the padded column pass
-hipError_t launch_rows_pad(const DevGeom& g, const PadJob& jb, hipStream_t st);
+// With psi and Q the source is x_kj = Q_j phi_kj of the angles from k_first on.
+hipError_t launch_rows_pad(const DevGeom& g, const PadJob& jb, hipStream_t st,
+                           const float2* psi = nullptr, const float2* Q = nullptr, int k_first = 0);
 hipError_t launch_cols_pad(const DevGeom& g, const PadJob& jb, double* Fpart, hipStream_t st);
 // Fourier-slice forward of nslab slabs of f.depth slices from z0 on (u: the
 // first slab's volume): psi of every angle of the call into
@@ -168,8 +170,6 @@ hipError_t launch_fs_adjoint(const DevGeom& g, const FsArgs& f, const float2* S,
                              hipStream_t st);
 hipError_t launch_copy_rows(const float2* src, size_t src_pitch, float2* dst, size_t rows,
                             int W, hipStream_t st);
-hipError_t launch_frames_x(const DevGeom& g, const float2* psi, const float2* Q, float2* X,
-                           int k_first, int Kc, hipStream_t st);
 hipError_t launch_frames_c(const DevGeom& g, float2* X, const float2* psi, const float2* Q,
                            float2* G, float2* Pbuf, int accumulate, int first, int split,
                            int k_first, int Kc, hipStream_t st);

@@ -587,8 +587,14 @@ __global__ __launch_bounds__(kThreads) void k_cols_gq(PropJobs jobs, float2* __r
 bool pad_size_supported(int n) { return fft_size_supported(n) && n <= 1024; }
 int pad_col_tiles(int H, int W) { return W / cols_tc(2 * H); }
 
-template <int W>
-__global__ __launch_bounds__(kThreads) void k_rows_pad(PadJob jb, DevGeom g) {
+// FX: the source is x_kj = Q_j phi_kj, formed here from psi and Q (pass A;
+// padded plans take no probe shifts).  In a kernel of its own that product
+// was written and read back once more: 256 px, 180 angles, 258 us of 2.94 ms,
+// now 2.72.
+template <int W, bool FX>
+__global__ __launch_bounds__(kThreads) void k_rows_pad(PadJob jb, const float2* __restrict__ psi,
+                                                       const float2* __restrict__ Q, int k_first,
+                                                       DevGeom g) {
   constexpr int N2 = 2 * W, TL = rows_tl(N2), LPW = rows_lpw(N2), E = N2 / TL;
   constexpr int OFF = W / 2;
   __shared__ float2 s_tw[fft_line_len(N2)];
@@ -600,11 +606,27 @@ __global__ __launch_bounds__(kThreads) void k_rows_pad(PadJob jb, DevGeom g) {
   // e in [E0, E1).
   static_assert(OFF % TL == 0 && W % TL == 0, "the centre is whole steps");
   constexpr int E0 = OFF / TL, E1 = (OFF + W) / TL;
-  const float2* in = jb.src + (size_t)f * jb.src_step + (size_t)z * W - OFF + lt;
   float2 v[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) v[e] = e >= E0 && e < E1 ? in[e * TL] : make_float2(0.f, 0.f);
   load_twiddles<N2, kThreads>(s_tw, g.tw2W);
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] = make_float2(0.f, 0.f);
+  if constexpr (FX) {
+    const int k = f / g.nd, j = f % g.nd;
+    double ty, tx;
+    shift_of(g, k_first + k, j, ty, tx);
+    const AxisTaps tyt = fwd_taps(g.cH, g.mag[j], ty, z, g.H);
+    const float2* psik = psi + (size_t)k * g.H * W;
+    const float2* Qrow = Q + ((size_t)j * g.H + z) * W;
+#pragma unroll
+    for (int e = E0; e < E1; ++e) {
+      const int s = lt + e * TL - OFF;
+      v[e] = cmul(Qrow[s], sample_phi(psik, W, tyt, fwd_taps(g.cW, g.mag[j], tx, s, W)));
+    }
+  } else {
+    const float2* in = jb.src + (size_t)f * jb.src_step + (size_t)z * W - OFF + lt;
+#pragma unroll
+    for (int e = E0; e < E1; ++e) v[e] = in[e * TL];
+  }
   float2* L = s_line[line];
   constexpr bool WL = wave_lines(TL);
   if constexpr (WL) __syncthreads();   // s_tw
@@ -701,34 +723,6 @@ __global__ __launch_bounds__(kColThreads, H == 384 || H == 1024 ? 2 : 4) void k_
   float2* out = jb.dst + (size_t)f * HW + s0 + t0;
 #pragma unroll
   for (int r = 0; r < NPT; ++r) out[(size_t)r * RS * W] = l0[r * LSTEP];
-}
-
-// x_kj = Q_kj phi_kj for every pixel of a chunk's frames (pass A without
-// its row transform).
-__global__ __launch_bounds__(kThreads) void k_frames_x(const float2* __restrict__ psi,
-                                                       const float2* __restrict__ Q,
-                                                       float2* __restrict__ X, DevGeom g,
-                                                       int k_first, int Kc) {
-  const size_t HW = (size_t)g.H * g.W;
-  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= HW * Kc * g.nd) return;
-  const size_t fidx = i / HW;
-  const int p = (int)(i % HW);
-  const int z = p / g.W, s = p % g.W;
-  const int k = (int)(fidx / g.nd), j = (int)(fidx % g.nd);
-  double ty, tx;
-  shift_of(g, k_first + k, j, ty, tx);
-  const double m = g.mag[j];
-  const AxisTaps tyt = fwd_taps(g.cH, m, ty, z, g.H);
-  const AxisTaps txt = fwd_taps(g.cW, m, tx, s, g.W);
-  float2 qv;
-  if (g.pshift) {
-    const float* ps = g.pshift + ((size_t)(k_first + k) * g.nd + j) * 2;
-    qv = sample_circ(Q + (size_t)j * HW, g.H, g.W, (double)z - ps[0], (double)s - ps[1]);
-  } else {
-    qv = Q[(size_t)j * HW + p];
-  }
-  X[i] = cmul(qv, sample_phi(psi + (size_t)k * HW, g.W, tyt, txt));
 }
 
 // Pass C without its row transform: for every pixel of plane j, over the
@@ -1056,12 +1050,19 @@ hipError_t launch_cols_gq(const DevGeom& g, const PropJobs& jobs, float2* gq, hi
 
 #define HOLO_FOR_PAD_SIZES(X) X(64) X(128) X(192) X(256) X(384) X(512) X(1024)
 
-hipError_t launch_rows_pad(const DevGeom& g, const PadJob& jb, hipStream_t st) {
+hipError_t launch_rows_pad(const DevGeom& g, const PadJob& jb, hipStream_t st, const float2* psi,
+                           const float2* Q, int k_first) {
   if (jb.nframes == 0) return hipSuccess;
-  if (!g.tw2W || !g.chirp2W) return hipErrorInvalidValue;
+  if (!g.tw2W || !g.chirp2W || (psi && (!Q || g.pshift))) return hipErrorInvalidValue;
   const dim3 grid(g.H / rows_lpw(2 * g.W), jb.nframes);
   switch (g.W) {
-#define CASE(N) case N: k_rows_pad<N><<<grid, kThreads, 0, st>>>(jb, g); break;
+#define CASE(N)                                                                        \
+  case N:                                                                              \
+    if (psi)                                                                           \
+      k_rows_pad<N, true><<<grid, kThreads, 0, st>>>(jb, psi, Q, k_first, g);          \
+    else                                                                               \
+      k_rows_pad<N, false><<<grid, kThreads, 0, st>>>(jb, nullptr, nullptr, 0, g);     \
+    break;
     HOLO_FOR_PAD_SIZES(CASE)
 #undef CASE
     default: return hipErrorInvalidValue;
@@ -1098,15 +1099,6 @@ hipError_t launch_copy_rows(const float2* src, size_t src_pitch, float2* dst, si
   if (n == 0) return hipSuccess;
   k_copy_rows<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, st>>>(src, src_pitch, dst,
                                                                               n, W);
-  return hipGetLastError();
-}
-
-hipError_t launch_frames_x(const DevGeom& g, const float2* psi, const float2* Q, float2* X,
-                           int k_first, int Kc, hipStream_t st) {
-  const size_t n = (size_t)g.H * g.W * Kc * g.nd;
-  if (n == 0) return hipSuccess;
-  k_frames_x<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, st>>>(psi, Q, X, g, k_first,
-                                                                            Kc);
   return hipGetLastError();
 }
 
