@@ -243,7 +243,8 @@ holo_status holo_plan_set_padding(holo_plan* plan, int32_t pad);
  *     approximation error a few 1e-8 relative) with O(W^2 log W + N_theta W)
  *     work per slice instead of O(N_theta W^2).  Its transpose is the exact
  *     transpose of the same computation.  Needs det_cols <= 1024; changes
- *     the workspace (8 grids of (2W)^2 and 8 N_theta (W + 2) samples in
+ *     the workspace (per 8 slices of a launch, grids of (2W)^2, N_theta
+ *     (W + 1) samples of each and partial tiles, for up to 64 MB of grids, in
  *     place of the ray sums' slice-blocked volume copies; query
  *     holo_workspace_bytes again).
  * Errors: INVALID_ARGUMENT (NULL plan, unknown value), UNSUPPORTED_SIZE
