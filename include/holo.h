@@ -120,9 +120,10 @@ holo_status holo_workspace_bytes(const holo_plan* plan, size_t* bytes);
 holo_status holo_plan_set_probe_shifts(holo_plan* plan, const float* shifts);
 
 /* Angles per chunk (the frames of one chunk are formed, back-propagated and
- * dropped before the next; the workspace grows with it).  Chunks of 32 angles
- * or more run several at a time while the frames of all their planes stay
- * within 128 MB, and the workspace is sized for that.  set_chunk changes
+ * dropped before the next; the workspace grows with it).  Where the frames
+ * of all planes are small, plans with chunks of 32 angles or more take as many
+ * angles at a time as stay within 128 MB, and the workspace is sized for that
+ * (it never shrinks as the chunk grows).  set_chunk changes
  * the plan's workspace size (query holo_workspace_bytes again); chunks below
  * the plan's largest forward angle group (at most 4 angles) are rejected
  * with INVALID_ARGUMENT; values above n_angles are clamped.  Host-only. */

@@ -239,8 +239,9 @@ static void layout_workspace(holo_plan* P) {
   const size_t fr = (size_t)P->H * P->W * sizeof(float2);
   size_t o = 0;
   P->off_Q = o;   o = align_up(o + fr * P->nd);
-  // Angles that go through the stages together: the plan's chunk, or as many
-  // whole chunks of at least 32 angles as keep the frames under 128 MB.  A
+  // Angles that go through the stages together: the plan's chunk, or, from 32
+  // angles on, as many as keep the frames under 128 MB if those are more (so
+  // the workspace never shrinks as the chunk grows).  A
   // 64-angle chunk of small frames leaves the chip half empty in every launch:
   // at 128 px and 180 angles the ray sums took 3 launches of 69 us, and take
   // one of 97; a five-iteration solve 4.07 -> 3.05 ms.  A caller who asks for
@@ -248,8 +249,7 @@ static void layout_workspace(holo_plan* P) {
   P->run_chunk = P->chunk;
   if (P->chunk >= 32)
     P->run_chunk = (int)std::min<size_t>(
-        P->n_angles,
-        P->chunk * std::max<size_t>(1, ((size_t)1 << 27) / (fr * P->nd * P->chunk)));
+        P->n_angles, std::max<size_t>(P->chunk, ((size_t)1 << 27) / (fr * P->nd)));
   const int chunk = P->run_chunk;
   P->c_split = pass_c_split(P->H, P->W, P->nd, chunk);
   P->off_G = o;   o = align_up(o + fr * P->nd * P->c_split);
