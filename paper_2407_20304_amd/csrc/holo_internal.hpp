@@ -49,7 +49,7 @@ struct DevGeom {
   // slices, [k][z / 64][re, im][(z / 8) % 8][bin][z % 8], with the slices'
   // largest magnitudes raised in smax; 0 (Fourier-slice) in rows, S[k][z][bin]
   int sino_blocked;
-  unsigned* smax;            // [H] bits of the largest |re|, |im| of every slice
+  unsigned* smax;            // [H] bits of the largest finite |re|, |im| of every slice
 };
 
 // Fourier-slice projector (holo_fs.hip): gridding kernel taps per axis,

@@ -798,7 +798,7 @@ __global__ __launch_bounds__(kThreads) void k_pass_d(const float2* __restrict__ 
   // zeros.  BLOCKED: the layout of the Joseph transpose,
   // [k][z / 64][re, im][(z / 8) % 8][kAdjPad + s][z % 8]; the 16 x 16 results
   // go through LDS so that each wave stores one 512-byte run, and the largest
-  // |re|, |im| of every slice is kept in g.smax.  Otherwise rows,
+  // finite |re|, |im| of every slice is kept in g.smax.  Otherwise rows,
   // S[k][z][kAdjPad + s].  The transposed resampling is separable, so its taps
   // are formed once per workgroup (once per angle with shifts): per plane,
   // the row taps of each of the 16 rows and the column taps of each of the
@@ -876,9 +876,10 @@ __global__ __launch_bounds__(kThreads) void k_pass_d(const float2* __restrict__ 
       h = make_float2(g.kappa * cy, -g.kappa * cx);
     }
     if constexpr (BLOCKED) {
-      // (fmaxf would drop a NaN: compared as bits below)
-      const unsigned hb = max(__float_as_uint(fabsf(h.x)), __float_as_uint(fabsf(h.y)));
-      big = __uint_as_float(max(__float_as_uint(big), hb));
+      // (an infinity or NaN does not set its slice's scale)
+      const float hx = fabsf(h.x), hy = fabsf(h.y);
+      if (hx < INFINITY) big = fmaxf(big, hx);
+      if (hy < INFINITY) big = fmaxf(big, hy);
       // two buffers by angle parity: the barrier of the next angle separates
       // this angle's reads from the writes after it
       s_out[k & 1][r][c] = h;

@@ -349,26 +349,35 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
 //                                      h[4 angles x 8 bins][slices x (re, im)]
 // is one 16 x 16 x 32 product per 8 slices.  Operands are single-precision
 // numbers split into two half-precision terms each, x = x1 + x2 (the second
-// term the rounded remainder: together 22 to 24 bits), multiplied as
-// w1 h1 + w1 h2 + w2 h1 with single-precision sums; the dropped w2 h2 is
-// below the last bit kept.  On the vector units the same sums took 8.6
-// instructions and 8 bytes of LDS reads per voxel, slice and angle against
-// 4 bytes and 24 products of 16 x 16 x 32 per 16 x 64 x 4 of them here: 345
-// -> 201 ms at 1024^3 x 1800 angles, conversion included.  Every slice of h is scaled by a power of two
-// (its largest value to 2^14 .. 2^15) and the weights by 2^kAdjWScale, so
-// that both terms are normal numbers down to 2^-17 of the largest value; the
-// result is scaled back exactly.
+// term the rounded remainder: x to one unit in its last place, 2^-23),
+// multiplied as w1 h1 + w1 h2 + w2 h1 with single-precision sums; the dropped
+// w2 h2 is at most 2^-22 of its product, a quarter of what single precision
+// leaves of a weight of 1 (positions of up to 21 bins, held to 2^-20).  On
+// the vector units the same sums took 8.6 instructions and 8 bytes of LDS
+// reads per voxel, slice and angle against 4 bytes and 24 products of
+// 16 x 16 x 32 per 16 x 64 x 4 of them here: 345 -> 201 ms at 1024^3 x 1800
+// angles, conversion included.  Every slice of h is scaled by a power of two
+// (its largest finite value to 2^14 .. 2^15) and the weights by
+// 2^kAdjWScale; h2 is stored times 2^kAdjTail and multiplied by w1
+// 2^-kAdjTail, so the two terms have about the same size and hold a sample to
+// one part in 2^21 down to 2^-30 of its slice's largest, and never worse
+// than 2^-51 of that (unscaled, second terms were lost from 2^-17 on).
+// The result is scaled back exactly.
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-// Power of two that brings a largest magnitude (its bits) to 2^14 .. 2^15,
-// within what a float holds together with its inverse; 1 for zero, infinity
-// and NaN.
+// Power of two of the second terms of h against their weights (a remainder
+// is at most 2^-11 of its sample: 2^12 keeps it below the largest half).
+constexpr int kAdjTail = 12;
+
+// Power of two that brings a largest finite magnitude (its bits) to
+// 2^14 .. 2^15, within what a float holds together with its inverse; 1 for
+// zero.
 __device__ __forceinline__ int split_exponent(unsigned bits) {
-  if (bits == 0u || bits >= 0x7f800000u) return 0;
+  if (bits == 0u) return 0;
   return min(14 - ((int)(bits >> 23) - 127), 120);
 }
 
@@ -381,8 +390,9 @@ __device__ __forceinline__ unsigned pack_half2(_Float16 a, _Float16 b) {
 // in the same memory.  Both are [k][z / 64][2][(z / 8) % 8][bin][z % 8]
 // words of 32 bits: pass D puts the real part in half 0 and the imaginary
 // part in half 1, the split form the first terms of both (two half-precision
-// numbers) in half 0 and the second terms in half 1.  The two words of a
-// sample are read and written by one thread.  Bound by HBM: 8 bytes read and
+// numbers) in half 0 and the second terms (times 2^kAdjTail) in half 1.  An
+// infinity or NaN stays one and leaves its slice's scale alone.  The two words
+// of a sample are read and written by one thread.  Bound by HBM: 8 bytes read and
 // written per bin and slice.
 __global__ __launch_bounds__(kThreads) void k_split_sino(unsigned* __restrict__ S,
                                                          const unsigned* __restrict__ smax,
@@ -404,7 +414,8 @@ __global__ __launch_bounds__(kThreads) void k_split_sino(unsigned* __restrict__ 
     const float u = x[c] * sc, v = y[c] * sc;
     const _Float16 u1 = (_Float16)u, v1 = (_Float16)v;
     a[c] = pack_half2(u1, v1);
-    b[c] = pack_half2((_Float16)(u - (float)u1), (_Float16)(v - (float)v1));
+    constexpr float tail = (float)(1 << kAdjTail);
+    b[c] = pack_half2((_Float16)((u - (float)u1) * tail), (_Float16)((v - (float)v1) * tail));
   }
   *reinterpret_cast<uint4*>(lo) = make_uint4(a[0], a[1], a[2], a[3]);
   *reinterpret_cast<uint4*>(hi) = make_uint4(b[0], b[1], b[2], b[3]);
@@ -564,7 +575,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
 
   // Operands of block b of group gi: the lane's 8 weights, and the LDS
   // address of its words of the block's first pair.
-  half8 a1, a2;
+  half8 a1, a2, at;                                 // w1, w2, w1 2^-kAdjTail
   unsigned bp;
   const unsigned lp = lds0 + (unsigned)((ga >> 1) * (ROWS * 32) + (m >> 2) * 64 + (ga & 1) * 32 + (m & 3) * 8);
   float minus1 = -1.0f;
@@ -585,8 +596,11 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
       asm volatile("" : "+v"(pu));
       const half2v p = __builtin_bit_cast(half2v, pu);
       const half2v r = {(_Float16)fmaf((float)p[0], minus1, u), (_Float16)fmaf((float)p[1], minus1, v)};
+      const half2v t = p * (half2v)((_Float16)(1.0f / (1 << kAdjTail)));
       a1[i] = p[0];
       a1[i + 1] = p[1];
+      at[i] = t[0];
+      at[i + 1] = t[1];
       a2[i] = r[0];
       a2[i + 1] = r[1];
     }
@@ -626,7 +640,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
       // multiplied, and the next block's weights are formed between the
       // products.
       constexpr int LA = 2;
-      const half8 w1 = a1, w2 = a2;
+      const half8 w1 = a1, w2 = a2, wt = at;
       auto* wp = (__attribute__((address_space(3))) short4v*)(uintptr_t)bp;
       half8 h1[NT], h2[NT];
       auto read8 = [&](int o) {                      // o: in 8 bytes; 8 bins of a column
@@ -649,7 +663,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
         if ((8 * b + t) % 2 == 1 && (8 * b + t) / 2 < LPW) issue((8 * b + t) / 2);
         const half8 x1 = h1[t], x2 = h2[t];
         acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2, x1, acc[b][t], 0, 0, 0);
-        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1, x2, acc[b][t], 0, 0, 0);
+        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wt, x2, acc[b][t], 0, 0, 0);
         acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1, x1, acc[b][t], 0, 0, 0);
       }
 #pragma unroll
@@ -659,7 +673,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
       }
     }
     // (formed above, not sunk below the branch)
-    asm volatile("" : "+v"(a1), "+v"(a2), "+v"(bp));
+    asm volatile("" : "+v"(a1), "+v"(a2), "+v"(at), "+v"(bp));
     const unsigned next = buf0;
     buf0 = buf1;
     buf1 = buf2;
