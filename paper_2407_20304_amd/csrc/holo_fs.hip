@@ -57,21 +57,6 @@ __device__ __forceinline__ float es_kernel(float x, float beta) {
   return r > 0.0f ? expf(beta * (sqrtf(r) - 1.0f)) : 0.0f;
 }
 
-// Position of a polar sample along one axis (grid units, frequency zero at
-// M/2): first of its KW taps and the distance of the sample from it.  Taps
-// start at floor(pos) - KW/2 + 1, so every distance lies in (-KW/2, KW/2].
-struct FsTap {
-  int i0;
-  float r;
-};
-__device__ __forceinline__ FsTap fs_tap(int m, double step, int M) {
-  const double gx = (double)m * step, fl = floor(gx);
-  FsTap t;
-  t.i0 = (int)fl - KW / 2 + 1 + M / 2;
-  t.r = (float)(gx - fl) + (float)(KW / 2 - 1);
-  return t;
-}
-
 __device__ __forceinline__ int wrap(int i, int M) { return i < 0 ? i + M : (i >= M ? i - M : i); }
 
 // lines[z][fpi(n)] <-> 64-byte records rec(n) of 8 slices: 4 threads per
@@ -207,8 +192,8 @@ __global__ __launch_bounds__(fs_nt(W), 4) void k_fs_project(const float2* __rest
     float wx[KW], wy[KW / 4];                         // wy: rows 4 b + q
 #pragma unroll
     for (int b = 0; b < KW / 4; ++b) {
-      const float x = es_kernel(tx.r - (float)(4 * b + q), beta);
-      wy[b] = es_kernel(ty.r - (float)(4 * b + q), beta);
+      const float x = es_kernel(fs_dist(tx.r, 4 * b + q), beta);
+      wy[b] = es_kernel(fs_dist(ty.r, 4 * b + q), beta);
 #pragma unroll
       for (int c = 0; c < 4; ++c) wx[4 * b + c] = __shfl(x, c, 4);
     }
@@ -339,7 +324,7 @@ __global__ __launch_bounds__(256) void k_fs_spread(const float2* __restrict__ A,
   __shared__ float s_wx[4 * kSpWave * KW], s_wy[4 * kSpWave * KW];
   __shared__ int s_ij[4 * kSpWave];                 // first taps relative to the tile
   __shared__ int s_src[4 * kSpWave];
-  __shared__ float2 s_r[4 * kSpWave];
+  __shared__ double2 s_r[4 * kSpWave];               // distances from the first taps
   __shared__ int s_cnt[4];
   const FsItem it = f.items[blockIdx.x];
   const int slab = blockIdx.y;
@@ -395,7 +380,7 @@ __global__ __launch_bounds__(256) void k_fs_spread(const float2* __restrict__ A,
         const int c = c0 + lane, li = l0 + 4 * wave + c / 20, j = c % 20;
         bool ok = c < 80 && li < hi;
         int kk = 0, m = 0;
-        FsTap ax{0, 0.f}, ay{0, 0.f};
+        FsTap ax{0, 0.0}, ay{0, 0.0};
         if (ok) {
           kk = f.sorted_k[li < n0 ? seg[0][0] + li : seg[1][0] + li - n0] - f.k0;
           ok = kk >= 0 && kk < f.K;
@@ -417,7 +402,7 @@ __global__ __launch_bounds__(256) void k_fs_spread(const float2* __restrict__ A,
           const int e = wave * kSpWave + cnt + __popcll(mask & ((1ull << lane) - 1));
           s_ij[e] = (ax.i0 & 0xffff) | (ay.i0 << 16);
           s_src[e] = kk * (W + 1) + m + W / 2;
-          s_r[e] = make_float2(ax.r, ay.r);
+          s_r[e] = make_double2(ax.r, ay.r);
         }
         cnt += __popcll(mask);
       }
@@ -427,9 +412,9 @@ __global__ __launch_bounds__(256) void k_fs_spread(const float2* __restrict__ A,
       // slices (4 lanes per sample)
       for (int i = lane; i < cnt * 8; i += 64) {
         const int e = wave * kSpWave + (i >> 3), b = i & 7;
-        const float2 r = s_r[e];
-        s_wx[e * KW + b] = es_kernel(r.x - (float)b, beta);
-        s_wy[e * KW + b] = es_kernel(r.y - (float)b, beta);
+        const double2 r = s_r[e];
+        s_wx[e * KW + b] = es_kernel(fs_dist(r.x, b), beta);
+        s_wy[e * KW + b] = es_kernel(fs_dist(r.y, b), beta);
       }
       for (int i = lane; i < cnt * 4; i += 64) {
         const int e = wave * kSpWave + (i >> 2);

@@ -7,6 +7,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "fs_taps.hpp"
+
 namespace holo {
 
 constexpr int kThreads = 256;   // threads per workgroup of the 1-D kernels
@@ -52,9 +54,8 @@ struct DevGeom {
   unsigned* smax;            // [H] bits of the largest finite |re|, |im| of every slice
 };
 
-// Fourier-slice projector (holo_fs.hip): gridding kernel taps per axis,
-// slices per slab, and the bins of the transpose's angle-window table.
-constexpr int kFsWidth = 8;
+// Fourier-slice projector (holo_fs.hip): slices per slab, and the bins of the
+// transpose's angle-window table.
 constexpr int kFsSlab = 8;
 constexpr int kFsBins = 4096;
 // One workgroup of the transpose's spread: a 16 x 16 tile of the grid, or
