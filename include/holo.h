@@ -151,7 +151,8 @@ holo_status holo_plan_autotune(holo_plan* plan, const holo_c64* u, const holo_c6
  *             default: 16 for H <= 512, 8 for H = 1024, 4 for H = 2048) or
  *             half of the default;
  *   FS_SLAB   slices per slab of the Fourier-slice projector: 1, 2, 4 or 8
- *             (default 8);
+ *             (default 8).  Kept and reported, without effect: the kernels
+ *             take 8 slices at a time whatever it says;
  *   FWD_BINS  bins per workgroup of the forward ray sums, 16 (default) or
  *             8 (smaller staged windows, so more angles share one;
  *             setting it regroups the angles, and it is refused if the chunk

@@ -66,7 +66,8 @@ struct holo_plan {
   // first sorted position of every angle bin
   int projector = HOLO_PROJECTOR_JOSEPH;
   // launch-shape choices (the autotuner's tiles): pass B's columns per
-  // workgroup (0 = default) and the Fourier-slice slab depth
+  // workgroup (0 = default), and the Fourier-slice slab depth (kept for its
+  // callers: every slab has kFsSlab slices)
   int col_tile = 0;
   int fs_slab = kFsSlab;
   // Joseph's forward of the next chunk on a second stream, concurrent with
@@ -289,7 +290,7 @@ static void layout_workspace(holo_plan* P) {
   // (128 px: 128 workgroups of 128 threads in a row pass)
   const size_t gb = (size_t)kFsSlab * M * M * sizeof(float2);
   P->fs_batch = (int)std::max<size_t>(
-      1, std::min<size_t>((size_t)P->H / P->fs_slab, ((size_t)1 << 26) / gb));
+      1, std::min<size_t>((size_t)P->H / kFsSlab, ((size_t)1 << 26) / gb));
   const size_t nb = fs ? (size_t)P->fs_batch : 0;
   P->off_fsG = o; o = align_up(o + nb * gb);
   P->off_fsA = o;
@@ -719,12 +720,11 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     fa.ang = d_ang;
     fa.sorted_k = (const int*)(tb + P->off_fssorted);
     fa.bin_first = (const int*)(tb + P->off_fsbins);
-    fa.depth = P->fs_slab;                  // divides H
     fa.n_items = (int)P->fs_items.size();
     fa.n_parts = P->fs_parts;
     fa.items = (const FsItem*)(tb + P->off_fsitems);
-    for (int z0 = 0; z0 < H; z0 += P->fs_slab * P->fs_batch) {
-      const int ns = std::min(P->fs_batch, (H - z0) / P->fs_slab);
+    for (int z0 = 0; z0 < H; z0 += kFsSlab * P->fs_batch) {
+      const int ns = std::min(P->fs_batch, (H - z0) / kFsSlab);
       HOLO_HIP(timed(P, HOLO_K_RADON_FWD, st, [&] {
         return launch_fs_forward(g, fa, u + (size_t)z0 * W * W, fsG, S, z0, ns, st);
       }));
@@ -897,8 +897,8 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
   }
   if (want_gu && fs) {
     float2* fsP = (float2*)(wsb + P->off_fsP);
-    for (int z0 = 0; z0 < H; z0 += P->fs_slab * P->fs_batch) {
-      const int ns = std::min(P->fs_batch, (H - z0) / P->fs_slab);
+    for (int z0 = 0; z0 < H; z0 += kFsSlab * P->fs_batch) {
+      const int ns = std::min(P->fs_batch, (H - z0) / kFsSlab);
       HOLO_HIP(timed(P, HOLO_K_RADON_ADJ, st, [&] {
         return launch_fs_adjoint(g, fa, S, fsA, fsG, fsP, gu + (size_t)z0 * W * W, z0, ns, st);
       }));

@@ -17,8 +17,8 @@
 // table of the angles sorted modulo pi, so no atomics and a fixed order),
 // inverse 2-D FFT, the centre W x W, divided by the kernel's transform.
 //
-// Slices are processed in slabs of at most kFsSlab = 8; the 8 slices of a
-// slab lie next to each other in its grid, G[y][x][slice], and in the
+// Slices are processed in slabs of kFsSlab = 8 (every supported height is a
+// multiple of 64); the 8 slices of a slab lie next to each other in its grid, G[y][x][slice], and in the
 // transpose's polar samples, A[angle][m][slice] (one 64-byte line per grid
 // point or sample), so positions and kernel weights are formed once for all
 // of them and every gather reads whole lines.  Frequency zero is at (M/2,
@@ -99,8 +99,7 @@ __global__ __launch_bounds__(fs_nt(2 * W)) void k_fs_rows(const float2* __restri
   const int z = threadIdx.x / TL, lt = threadIdx.x % TL;
   const int y = blockIdx.x, slab = blockIdx.y;
   for (int i = threadIdx.x; i < M; i += NT) s_tw[fpi(i)] = tw[i];
-  const bool live = z < f.depth;
-  const float2* row = u + ((size_t)(slab * f.depth + (live ? z : 0)) * W + y) * W;
+  const float2* row = u + ((size_t)(slab * SL + z) * W + y) * W;
   const float dy = (y & 1) != 0 ? -f.dinv[y] : f.dinv[y];   // W/2 is even
   float2 v[E];
 #pragma unroll
@@ -108,7 +107,7 @@ __global__ __launch_bounds__(fs_nt(2 * W)) void k_fs_rows(const float2* __restri
     const int n = lt + e * TL;
     const int xp = n < W / 2 ? n : n - M;             // x' of grid column n
     v[e] = make_float2(0.f, 0.f);
-    if (live && xp >= -W / 2 && xp < W / 2) {
+    if (xp >= -W / 2 && xp < W / 2) {
       const int x = xp + W / 2;
       const float s = (x & 1) != 0 ? -dy * f.dinv[x] : dy * f.dinv[x];
       const float2 a = row[x];
@@ -235,10 +234,9 @@ __global__ __launch_bounds__(fs_nt(W), 4) void k_fs_project(const float2* __rest
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = Ln[fpi(lt + e * TL)];
   fft_e<W, TL, true, true, true>(v, Ln, s_tw, lt);
-  if (z >= f.depth) return;
   const double twopi = 6.283185307179586476925;
   const int Wp = W + 2 * kAdjPad;
-  float2* out = S + ((size_t)k * H + z0 + slab * f.depth + z) * Wp + kAdjPad;
+  float2* out = S + ((size_t)k * H + z0 + slab * SL + z) * Wp + kAdjPad;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const float2 p = v[e];
@@ -270,11 +268,10 @@ __global__ __launch_bounds__(fs_nt(W)) void k_fs_line_T(const float2* __restrict
   const int k = blockIdx.x, slab = blockIdx.y;
   for (int i = threadIdx.x; i < W; i += NT) s_tw[fpi(i)] = twW[i];
   const int Wp = W + 2 * kAdjPad;
-  const bool live = z < f.depth;
-  const float2* in = S + ((size_t)k * H + z0 + slab * f.depth + (live ? z : 0)) * Wp + kAdjPad;
+  const float2* in = S + ((size_t)k * H + z0 + slab * SL + z) * Wp + kAdjPad;
   float2 v[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) v[e] = live ? in[lt + e * TL] : make_float2(0.f, 0.f);
+  for (int e = 0; e < E; ++e) v[e] = in[lt + e * TL];
   __syncthreads();
   float2* Ln = s_line + z * fs_pitch(W);
   fft_e<W, TL, false, true, true>(v, Ln, s_tw, lt);
@@ -504,9 +501,8 @@ __global__ __launch_bounds__(fs_nt(2 * W)) void k_fs_rows_T(const float2* __rest
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = Ln[fpi(lt + e * TL)];
   fft_e<M, TL, true, true, true>(v, Ln, s_tw, lt);
-  if (z >= f.depth) return;
   const float dy = (y & 1) != 0 ? -f.dinv[y] : f.dinv[y];
-  float2* out = gu + ((size_t)(slab * f.depth + z) * W + y) * W;
+  float2* out = gu + ((size_t)(slab * SL + z) * W + y) * W;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int n = lt + e * TL;
@@ -564,7 +560,7 @@ bool fs_size_supported(int W) {
 
 hipError_t launch_fs_forward(const DevGeom& g, const FsArgs& f, const float2* u, float2* G,
                              float2* S, int z0, int nslab, hipStream_t st) {
-  if (!g.tw2W || f.depth < 1 || f.depth > SL || nslab < 1) return hipErrorInvalidValue;
+  if (!g.tw2W || nslab < 1 || z0 + nslab * SL > g.H) return hipErrorInvalidValue;
   const unsigned ns = (unsigned)nslab;
   switch (g.W) {
 #define CASE(N)                                                                                 \
@@ -585,7 +581,7 @@ hipError_t launch_fs_forward(const DevGeom& g, const FsArgs& f, const float2* u,
 hipError_t launch_fs_adjoint(const DevGeom& g, const FsArgs& f, const float2* S, float2* A,
                              float2* G, float2* Part, float2* gu, int z0, int nslab,
                              hipStream_t st) {
-  if (!g.tw2W || f.depth < 1 || f.depth > SL || nslab < 1) return hipErrorInvalidValue;
+  if (!g.tw2W || nslab < 1 || z0 + nslab * SL > g.H) return hipErrorInvalidValue;
   const unsigned ns = (unsigned)nslab;
   switch (g.W) {
 #define CASE(N)                                                                                 \

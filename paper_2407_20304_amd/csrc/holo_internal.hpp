@@ -66,7 +66,6 @@ struct FsItem {
 };
 struct FsArgs {
   int K, k0;                 // the call's angles: plan angles k0 .. k0 + K - 1
-  int depth;                 // slices per slab (at most kFsSlab)
   int n_items, n_parts;      // spread items; partial grids per slab
   const FsItem* items;       // shared tiles first
   int n_angles;              // plan angles
@@ -157,7 +156,7 @@ int pad_col_tiles(int H, int W);  // column tiles per frame of the padded column
 hipError_t launch_rows_pad(const DevGeom& g, const PadJob& jb, hipStream_t st,
                            const float2* psi = nullptr, const float2* Q = nullptr, int k_first = 0);
 hipError_t launch_cols_pad(const DevGeom& g, const PadJob& jb, double* Fpart, hipStream_t st);
-// Fourier-slice forward of nslab slabs of f.depth slices from z0 on (u: the
+// Fourier-slice forward of nslab slabs of kFsSlab slices from z0 on (u: the
 // first slab's volume): psi of every angle of the call into
 // S[k][z][kAdjPad + s]; and its transpose from h in S into g_u of those
 // slices.  Per slab, G: kFsSlab grids of (2W)^2; A: kFsSlab * n_angles *
