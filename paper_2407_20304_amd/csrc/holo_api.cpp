@@ -54,6 +54,7 @@ struct holo_plan {
   std::vector<float> pshift;                // probe shifts, empty = none
   bool pshift_dirty = false;                // device copy older than pshift
   int fwd_nb = kFwdNB;                      // bins per forward workgroup (16 or 8)
+  bool fwd_auto = true;                     // fwd_nb is the default, not the caller's
   bool groups_dirty = false;                // device copy older than groups
   std::vector<double> ang;                  // [n_angles][kAngleStride]
   std::vector<float2> twW, twH, chirpW, chirpH;
@@ -233,6 +234,19 @@ static void set_fwd_bins(holo_plan* P, int nb) {
   P->fwd_nb = nb;
   form_groups(P, nb, P->groups, P->group_of, P->max_group);
   P->groups_dirty = true;
+}
+
+// Bins per forward workgroup of the plan's launches.  The caller's choice, or,
+// by default, 16 unless one launch over all of the plan's angles would be
+// fewer than two 16-bin workgroups per CU, which then take 8 bins (on the same
+// groups; the windows are narrower): twice as many, each with half the work
+// between a row's barriers.  96 workgroups of 16 bins (64 px, 90 angles) 41.3
+// -> 35.4 us, 240 (128 px) 74.8 -> 68.6 us, but 704 (256 px) 256 -> 325.  The
+// width changes the rounding of the taps, so the plan decides and not the
+// launch: an angle's fields do not depend on the chunk they are formed in.
+static int fwd_launch_bins(const holo_plan* P) {
+  const size_t n16 = (size_t)(P->W / kFwdNB) * (P->H / kFwdZT) * P->groups.size();
+  return P->fwd_auto && n16 < 512 ? kFwdNB / 2 : P->fwd_nb;
 }
 
 // Workspace layout of a plan (depends on its chunk).
@@ -782,6 +796,7 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     HOLO_HIP(hipEventRecord(P->ov_ev[0], st));
     HOLO_HIP(hipStreamWaitEvent(sf, P->ov_ev[0], 0));
   }
+  const int fwd_bins = fwd_launch_bins(P);
   hipEvent_t* ev_fwd = P->ov_ev + 1;      // [chunk parity]: forward done
   hipEvent_t* ev_frames = P->ov_ev + 3;   // [chunk parity]: its frames done
   auto forward = [&](size_t ci) -> hipError_t {
@@ -789,7 +804,7 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     const int gfirst = P->group_of[c0], glast = P->group_of[c1 - 1];
     hipError_t e = timed(P, HOLO_K_RADON_FWD, sf, [&] {
       return launch_radon_fwd(g, ub, uTb, psib[ci & 1], d_ang, d_groups, gfirst,
-                              glast - gfirst + 1, c0, c1, P->fwd_nb, sf);
+                              glast - gfirst + 1, c0, c1, fwd_bins, sf);
     });
     if (e == hipSuccess && ovl) e = hipEventRecord(ev_fwd[ci & 1], sf);
     return e;
@@ -1281,7 +1296,10 @@ static void tile_put(holo_plan* P, int param, int value) {
   else if (param == HOLO_TUNE_COL_TILE) P->col_tile = value;
   else if (param == HOLO_TUNE_FS_SLAB) P->fs_slab = value;
   else if (param == HOLO_TUNE_OVERLAP) P->overlap = value;
-  else if (value != P->fwd_nb) set_fwd_bins(P, value);
+  else {
+    P->fwd_auto = false;
+    if (value != P->fwd_nb) set_fwd_bins(P, value);
+  }
   layout_workspace(P);
 }
 
@@ -1325,17 +1343,22 @@ extern "C" holo_status holo_plan_autotune_tile(holo_plan* P, int32_t param, cons
   if (param < HOLO_TUNE_CHUNK || param > HOLO_TUNE_OVERLAP)
     return fail(HOLO_ERR_INVALID_ARGUMENT, "holo_plan_autotune: unknown parameter");
   const int chunk0 = tile_get(P, param);
+  const bool auto0 = P->fwd_auto;
+  auto put_back = [&] {
+    tile_put(P, param, chunk0);
+    P->fwd_auto = auto0;
+  };
   size_t need = 0;
   for (int i = 0; i < n_cand; ++i) {
     s = tile_check(P, param, candidates[i], "holo_plan_autotune");
     if (s != HOLO_OK) {
-      tile_put(P, param, chunk0);
+      put_back();
       return s;
     }
     tile_put(P, param, candidates[i]);
     need = std::max(need, P->ws_bytes);
   }
-  tile_put(P, param, chunk0);
+  put_back();
   if (ws_bytes < need)
     return fail(HOLO_ERR_WORKSPACE_TOO_SMALL, "holo_plan_autotune: workspace needs " +
                                                   std::to_string(need) + " bytes, got " +
@@ -1375,8 +1398,12 @@ extern "C" holo_status holo_plan_autotune_tile(holo_plan* P, int32_t param, cons
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  tile_put(P, param, s == HOLO_OK ? best : chunk0);
-  if (s == HOLO_OK) *best_chunk = best;
+  if (s == HOLO_OK) {
+    tile_put(P, param, best);
+    *best_chunk = best;
+  } else {
+    put_back();
+  }
   return s;
 }
 

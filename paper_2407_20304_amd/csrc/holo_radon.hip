@@ -715,13 +715,8 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
 hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uTb, float2* psi,
                             const double* ang, const int2* groups, int g0, int ngroups, int c0,
                             int c1, int nb, hipStream_t st) {
-  const unsigned n16 = (unsigned)(g.W / kFwdNB) * (unsigned)(g.H / kFwdZT) * (unsigned)ngroups;
-  // Grids of fewer than two 16-bin workgroups per CU take 8-bin ones (the same
-  // groups; the windows are narrower): twice as many, each with half the work
-  // between a row's barriers.  96 workgroups of 16 bins (64 px, 90 angles)
-  // 41.3 -> 35.4 us, 240 (128 px) 74.8 -> 68.6 us, but 704 (256 px) 256 -> 325.
-  if (nb == kFwdNB && n16 < 512) nb = kFwdNB / 2;
-  const unsigned n = n16 * (unsigned)(kFwdNB / nb);
+  if (nb < 1) return hipErrorInvalidValue;
+  const unsigned n = (unsigned)(g.W / nb) * (unsigned)(g.H / kFwdZT) * (unsigned)ngroups;
   if (nb == kFwdNB)
     k_radon_fwd<kFwdNB><<<n, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0, c1);
   else if (nb == kFwdNB / 2)
