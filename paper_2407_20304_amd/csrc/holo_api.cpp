@@ -766,6 +766,10 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     if (c1 == c0) c1 = std::min(c0 + P->run_chunk, k1);
     chunks.push_back(make_int2(c0, c1));
   }
+  // slots of the probe-gradient sums of this call: no more than the angles of
+  // its largest chunk (the others would be written and added as zeros)
+  int split = 1;
+  for (const int2& c : chunks) split = std::max(split, std::min(P->c_split, c.y - c.x));
   // With the overlap on, chunk i + 1's forward runs on the side stream
   // (into the other psi buffer) while chunk i's frame passes run on the
   // caller's stream: the forward waits for the frames that last read its
@@ -853,12 +857,11 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
         const PadJob ra = pj(X, X, hw, nf, chirp_det(0), nd, 1, 0, nullptr, 0);
         HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] { return launch_rows_pad(g, ra, st); }));
         HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-          return launch_frames_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, first, P->c_split, c0,
-                                 Kc, st);
+          return launch_frames_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, first, split, c0, Kc, st);
         }));
         if (want_gq && Pbuf)
           HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-            return launch_probe_shift_acc(g, Gacc, Pbuf, first, P->c_split, c0, Kc, st);
+            return launch_probe_shift_acc(g, Gacc, Pbuf, first, split, c0, Kc, st);
           }));
         if (want_gu)
           HOLO_HIP(timed(P, HOLO_K_PASS_D, st, [&] {
@@ -896,12 +899,11 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     }
     if ((mode == kGrad || mode == kAdj) && frames_back) {
       HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-        return launch_pass_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, first, P->c_split, c0, Kc,
-                             st);
+        return launch_pass_c(g, X, psi_c, Q, Gacc, Pbuf, want_gq ? 1 : 0, first, split, c0, Kc, st);
       }));
       if (want_gq && Pbuf)
         HOLO_HIP(timed(P, HOLO_K_PASS_C, st, [&] {
-          return launch_probe_shift_acc(g, Gacc, Pbuf, first, P->c_split, c0, Kc, st);
+          return launch_probe_shift_acc(g, Gacc, Pbuf, first, split, c0, Kc, st);
         }));
       if (want_gu)
         HOLO_HIP(timed(P, HOLO_K_PASS_D, st, [&] {
@@ -926,9 +928,9 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     }));
   }
   if (want_gq) {
-    if (P->c_split > 1)
+    if (split > 1)
       HOLO_HIP(timed(P, HOLO_K_OTHER, st, [&] {
-        return launch_sum_slots(Gacc, P->c_split, nd * HW, st);
+        return launch_sum_slots(Gacc, split, nd * HW, st);
       }));
     if (padded) {
       const int cp = chirp_probe(nd, 0);
