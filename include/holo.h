@@ -156,9 +156,9 @@ holo_status holo_plan_autotune(holo_plan* plan, const holo_c64* u, const holo_c6
  *   FWD_BINS  bins per workgroup of the forward ray sums, 16 (default) or
  *             8 (smaller staged windows, so more angles share one;
  *             setting it regroups the angles, and it is refused if the chunk
- *             is smaller than the new largest group).  Until it is set, a plan
- *             with fewer than 512 workgroups of 16 bins over all its angles
- *             runs 8-bin ones on the groups of 16 bins (reported as 16).
+ *             is smaller than the new largest group).  Until it is set,
+ *             launches of fewer than 512 workgroups take each block of 16 in
+ *             two halves, with the same bits.
  *   OVERLAP   1: Joseph's forward ray sums of the next chunk run on a second
  *             stream of the library's, concurrently with the current chunk's
  *             frame passes (two psi buffers in the workspace; the calls still

@@ -236,19 +236,6 @@ static void set_fwd_bins(holo_plan* P, int nb) {
   P->groups_dirty = true;
 }
 
-// Bins per forward workgroup of the plan's launches.  The caller's choice, or,
-// by default, 16 unless one launch over all of the plan's angles would be
-// fewer than two 16-bin workgroups per CU, which then take 8 bins (on the same
-// groups; the windows are narrower): twice as many, each with half the work
-// between a row's barriers.  96 workgroups of 16 bins (64 px, 90 angles) 41.3
-// -> 35.4 us, 240 (128 px) 74.8 -> 68.6 us, but 704 (256 px) 256 -> 325.  The
-// width changes the rounding of the taps, so the plan decides and not the
-// launch: an angle's fields do not depend on the chunk they are formed in.
-static int fwd_launch_bins(const holo_plan* P) {
-  const size_t n16 = (size_t)(P->W / kFwdNB) * (P->H / kFwdZT) * P->groups.size();
-  return P->fwd_auto && n16 < 512 ? kFwdNB / 2 : P->fwd_nb;
-}
-
 // Workspace layout of a plan (depends on its chunk).
 static void layout_workspace(holo_plan* P) {
   const size_t fr = (size_t)P->H * P->W * sizeof(float2);
@@ -800,7 +787,6 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     HOLO_HIP(hipEventRecord(P->ov_ev[0], st));
     HOLO_HIP(hipStreamWaitEvent(sf, P->ov_ev[0], 0));
   }
-  const int fwd_bins = fwd_launch_bins(P);
   hipEvent_t* ev_fwd = P->ov_ev + 1;      // [chunk parity]: forward done
   hipEvent_t* ev_frames = P->ov_ev + 3;   // [chunk parity]: its frames done
   auto forward = [&](size_t ci) -> hipError_t {
@@ -808,7 +794,7 @@ holo_status run(holo_plan* P, Mode mode, const holo_c64* u_, const holo_c64* q_,
     const int gfirst = P->group_of[c0], glast = P->group_of[c1 - 1];
     hipError_t e = timed(P, HOLO_K_RADON_FWD, sf, [&] {
       return launch_radon_fwd(g, ub, uTb, psib[ci & 1], d_ang, d_groups, gfirst,
-                              glast - gfirst + 1, c0, c1, fwd_bins, sf);
+                              glast - gfirst + 1, c0, c1, P->fwd_nb, P->fwd_auto, sf);
     });
     if (e == hipSuccess && ovl) e = hipEventRecord(ev_fwd[ci & 1], sf);
     return e;

@@ -191,9 +191,11 @@ hipError_t launch_sum_slots(float2* G, int ns, size_t n, hipStream_t st);
 hipError_t launch_cols_gq(const DevGeom& g, const PropJobs& jobs, float2* gq, hipStream_t st);
 hipError_t launch_pass_d(const DevGeom& g, const float2* X, const float2* psi, float2* S,
                          int k_first, int Kc, hipStream_t st);
+// Workgroups of nb bins; by_size: small launches may take halves of the 16-bin
+// blocks (the same results).
 hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uTb, float2* psi,
                             const double* ang, const int2* groups, int g0, int ngroups, int c0,
-                            int c1, int nb, hipStream_t st);
+                            int c1, int nb, bool by_size, hipStream_t st);
 // Transpose of the ray sums over angles k0 .. k0 + K - 1: S holds their
 // sinogram in pass D's blocked layout (overwritten by its split form), ang
 // the plan's whole angle table, smax the slices' largest magnitudes.

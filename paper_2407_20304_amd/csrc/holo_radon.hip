@@ -95,7 +95,12 @@ __global__ __launch_bounds__(kThreads) void k_block_volume(const float2* __restr
 // one column: free of bank conflicts.  Angles that walk along x read the
 // x/y-transposed volume, so both walk directions use the same code.  The
 // host groups angles so that every window fits.
-template <int NB>
+// HALF (NB = 8, W at most kHalfMaxW): half of a 16-bin block, with windows of
+// its own.  Tap positions are taken from the lowest column of the whole
+// block's window and its thread's first bin, so every tap and weight, and
+// with them the fields, are the bits that a 16-bin workgroup gives.
+constexpr int kHalfMaxW = 1024;
+template <int NB, bool HALF>
 __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restrict__ u,
                                                          const float2* __restrict__ uT,  // z-blocked
                                                          float2* __restrict__ psi, DevGeom g,
@@ -109,8 +114,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   constexpr int LPW = ROWF2 / (4 * 128);            // LDS-direct loads (16 B per lane) per wave per row
   constexpr int C4 = ZT / 2;                        // float4 per staged column
   static_assert(ZT == 64 && (NB == 16 || NB == 8) && LPW == 4 && kThreads == 256, "tiling");
+  static_assert(!HALF || NB == 8, "half of a 16-bin block");
   __shared__ float4 tile4[NBUF * ROWF2 / 2];
   __shared__ unsigned short s_win[kMaxW];           // 16 (xl + 64) + pairs of columns - 1
+  // HALF: first column of the window minus that of the whole block (0 where
+  // the window was moved)
+  __shared__ unsigned char s_dx[HALF ? kHalfMaxW : 1];
   __shared__ int s_first, s_last;                   // rows whose window meets the volume
   const int W = g.W, H = g.H;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -131,14 +140,17 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   const double* aw = ang + (size_t)k * kAngleStride;
   const float2* vol = (aw[kBranch] != 0.0) ? uT : u;
   const double B = aw[kB], D = aw[kD];
-  const double fA = aw[kA] + (double)s0 * B;
+  // base bin of the thread's tap positions, and its own first bin from there
+  const int sB = HALF ? s0 & ~3 : s0;
+  const float bo = HALF ? (float)(s0 & 3) : 0.f;
+  const double fA = aw[kA] + (double)sB * B;
   const float Bf = (float)B;
   // Range of the per-row base that keeps every tap of the thread's bins and
   // its right neighbour inside the staged window.  Inside the volume the
   // host's grouping keeps every tap at least one column inside the window,
   // so the clamp changes nothing there; a window moved into the zero
   // padding reads zeros wherever the taps land.
-  const float span = (float)(BPT - 1) * Bf;
+  const float span = (float)((HALF ? 4 : BPT) - 1) * Bf;
   const float rel_lo = fmaxf(0.0f, -span), rel_hi = (float)(SEG - 1) - fmaxf(0.0f, span) - 0.01f;
 
   // Window of every row, over the group's angles and the block's end bins:
@@ -154,7 +166,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   for (int r0 = 0; r0 < W; r0 += kThreads) {
     const int r = r0 + (int)threadIdx.x;            // W is a multiple of 64
     if (r - lane >= W) break;
-    double mn = 1e300, mx = -1e300;
+    double mn = 1e300, mx = -1e300, mn16 = 1e300;
 #pragma unroll
     for (int a = 0; a < kFwdNA; ++a) {              // (unrolled: the loads go together)
       const double* ap = ang + (size_t)(gf + min(a, na - 1)) * kAngleStride;
@@ -162,11 +174,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
       const double f0 = fr + (double)sb * ap[kB], f1 = fr + (double)(sb + NB - 1) * ap[kB];
       mn = fmin(mn, fmin(f0, f1));
       mx = fmax(mx, fmax(f0, f1));
+      if constexpr (HALF)
+        mn16 = fmin(mn16, fmin(fr + (double)(sb & ~15) * ap[kB], fr + (double)(sb | 15) * ap[kB]));
     }
     const int lo = (int)floor(mn) - 1, hi = (int)floor(mx) + 2;   // columns lo .. hi
     const int xl = min(max(lo, -kFwdPad), W + kFwdPad - SEG);
     const int pairs = xl == lo ? min((hi - lo + 2) / 2, SEG / 2) : SEG / 2;
     s_win[r] = (unsigned short)(16 * (xl + 64) + pairs - 1);
+    if constexpr (HALF) s_dx[r] = (unsigned char)(xl == lo ? lo - ((int)floor(mn16) - 1) : 0);
     const unsigned long long in = __ballot(hi >= 0 && lo < W);
     if (in) {
       first = min(first, r - lane + __builtin_ctzll(in));
@@ -199,8 +214,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   const int wv = __builtin_amdgcn_readfirstlane(wave);
   // loads of row y (its s_win entry: win) into buffer buf; returns how many
   // this wave issued
+  auto xl_of = [](int win) { return ((HALF ? win & 0xffff : win) >> 4) - 64; };
   auto issue = [&](int y, int win, int buf) {
-    const int xl = (win >> 4) - 64, n = ((win & 15) + 4 - wv) >> 2;
+    const int xl = xl_of(win), n = ((win & 15) + 4 - wv) >> 2;
     const float2* row = vl + ((ptrdiff_t)y * Wf + xl) * ZB;
     const unsigned dst = lds0 + (unsigned)((buf * (ROWF2 / 2) + wv * 64) * 16);
     auto load = [&](int i) {
@@ -243,9 +259,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
 #pragma unroll
     for (int e = 0; e < 4; ++e) { ax[b][e] = ay[b][e] = 0.f; ox[b][e] = oy[b][e] = 0.0; }
 
-  auto win_of = [&](int y) {
-    return __builtin_amdgcn_readfirstlane((int)s_win[min(y, W - 1)]);
+  // a row's window, HALF: with s_dx above it
+  auto win_at = [&](int y) {
+    const int r = min(y, W - 1);
+    return HALF ? (int)s_win[r] | (int)s_dx[r] << 16 : (int)s_win[r];
   };
+  auto win_of = [&](int y) { return __builtin_amdgcn_readfirstlane(win_at(y)); };
   // windows of rows y, y + 1 and y + 2 (read from LDS a row before use)
   int win0 = win_of(y_beg), win1 = win_of(y_beg + 1), win2 = win_of(y_beg + 2);
   int cur = 0, fly = 0;                             // buffer of row y; loads of row y + 1
@@ -260,20 +279,21 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     fly = y + 2 < y_end ? issue(y + 2, win2, cur == 0 ? 2 : cur - 1) : 0;
-    const int win3 = (int)s_win[min(y + 3, W - 1)];
+    const int win3 = win_at(y + 3);
     if (active) {
       // tap position of the thread's first bin relative to the window, in
       // double precision; the other bins add b B (< 4 sqrt(2))
-      float rel = (float)(fA + (double)y * D - (double)((win0 >> 4) - 64));
+      const int dx = HALF ? win0 >> 16 : 0;
+      float rel = (float)(fA + (double)y * D - (double)(xl_of(win0) - dx));
       rel = fminf(fmaxf(rel, rel_lo), rel_hi);
-      int tb = cur * (ROWF2 / 2) + pz;
+      int tb = cur * (ROWF2 / 2) + pz - dx * C4;
       asm volatile("" : "+v"(tb));                     // one base register per row
       const float4* tr = tile4 + tb;
       // software pipeline: the taps of bin b + 1 are requested before bin b
       // is accumulated
       float4 v[BPT][2][2];                             // [bin][pair][tap]
       auto fetch_bin = [&](int b) {
-        const float q = fmaf((float)b, Bf, rel);          // >= 0, < SEG - 1
+        const float q = fmaf(bo + (float)b, Bf, rel);     // >= dx, < dx + SEG - 1
         const float4* tp = tr + (int)q * C4;             // truncation = floor here
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
@@ -285,7 +305,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
 #pragma unroll
       for (int b = 0; b < BPT; ++b) {
         if (b + 1 < BPT) fetch_bin(b + 1);
-        const float w1 = __builtin_amdgcn_fractf(fmaf((float)b, Bf, rel)), w0 = 1.0f - w1;
+        const float w1 = __builtin_amdgcn_fractf(fmaf(bo + (float)b, Bf, rel)), w0 = 1.0f - w1;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
           const float4 t0 = v[b][p][0], t1 = v[b][p][1];
@@ -714,14 +734,20 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
 
 hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uTb, float2* psi,
                             const double* ang, const int2* groups, int g0, int ngroups, int c0,
-                            int c1, int nb, hipStream_t st) {
-  if (nb < 1) return hipErrorInvalidValue;
-  const unsigned n = (unsigned)(g.W / nb) * (unsigned)(g.H / kFwdZT) * (unsigned)ngroups;
-  if (nb == kFwdNB)
-    k_radon_fwd<kFwdNB><<<n, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0, c1);
-  else if (nb == kFwdNB / 2)
-    k_radon_fwd<kFwdNB / 2><<<n, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0,
-                                                    c1);
+                            int c1, int nb, bool by_size, hipStream_t st) {
+  const unsigned n16 = (unsigned)(g.W / kFwdNB) * (unsigned)(g.H / kFwdZT) * (unsigned)ngroups;
+  const unsigned n8 = n16 * (kFwdNB / 8);
+  // Grids of fewer than two 16-bin workgroups per CU take halves of them: twice
+  // as many, each with half the work between a row's barriers.  96 workgroups
+  // of 16 bins (64 px, 90 angles) 41.3 -> 35.4 us, 240 (128 px) 74.8 -> 68.6
+  // us, but 704 (256 px) 256 -> 325.
+  if (nb == 8)
+    k_radon_fwd<8, false><<<n8, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0, c1);
+  else if (nb == kFwdNB && by_size && n16 < 512 && g.W <= kHalfMaxW)
+    k_radon_fwd<8, true><<<n8, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0, c1);
+  else if (nb == kFwdNB)
+    k_radon_fwd<kFwdNB, false><<<n16, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups,
+                                                         c0, c1);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

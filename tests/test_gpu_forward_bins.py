@@ -1,6 +1,7 @@
-"""Bins per workgroup of the forward ray sums: the plan decides, so an angle's
-fields are the same bits in every chunk and range of whole groups, and a
-value that the caller sets is the one that runs."""
+"""Bins per workgroup of the forward ray sums: an angle's fields are the same
+bits in every chunk and range of whole groups, also where small launches take
+the 16-bin blocks in halves; a value that the caller sets is the one that
+runs."""
 
 import numpy as np
 import pytest
@@ -16,7 +17,7 @@ def _problem(W, n):
     rng = np.random.default_rng(4)
     p.u = (rng.uniform(0, 2e-6, p.u.shape) * (1 + 0.01j)).astype(np.complex64)
     g = p.geom
-    p.geom = O.Geometry(H=64, W=W, theta=np.arange(n) * (np.pi / n), mag_rel=g.mag_rel, m0=g.m0,
+    p.geom = O.Geometry(H=64, W=W, theta=np.arange(n) * (np.pi / n) if np.ndim(n) == 0 else n, mag_rel=g.mag_rel, m0=g.m0,
                         fresnel0=g.fresnel0, kappa=g.kappa)
     return p
 
@@ -27,12 +28,22 @@ def _fields(plan, p, *k):
     return plan.holo_fwd(torch.from_numpy(p.u).to(dev), torch.from_numpy(p.q).to(dev), *k).cpu().numpy()
 
 
-@pytest.mark.parametrize("W,n", [(64, 90), (512, 70)])     # 8 bins, 16 bins by default
+EDGES = np.array([0.0, 1e-9, np.pi / 4 - 1e-6, np.pi / 4, np.pi / 4 + 1e-6, np.pi / 2, 2.2, 3 * np.pi / 4,
+                  3.0, np.pi, -0.8, -2.4])
+
+
+# 64 px: halves in every launch; 512: in short ones; edges: axes, the walk
+# switch, windows outside the volume at either end
+@pytest.mark.parametrize("W,n", [(64, 90), (512, 70), (192, EDGES), (1024, EDGES[:7])], ids=str)
 def test_the_same_bits_in_every_chunk_and_range(W, n):
     p = _problem(W, n)
+    n = len(p.geom.theta)
+    whole = gpu_plan(p)
+    whole.set_chunk(n)
+    whole.set_tile("fwd_bins", 16)
+    v = _fields(whole, p)
     plan = gpu_plan(p)
-    plan.set_chunk(n)
-    v = _fields(plan, p)
+    assert (_fields(plan, p) == v).all()
     groups = plan.ray_groups()
     k0, k1 = groups[-4][0], groups[-1][0]
     assert (_fields(plan, p, k0, k1) == v[k0:k1]).all()
@@ -54,6 +65,6 @@ def test_a_set_value_runs():
     v["8"] = _fields(plan, p)
     for name, x in v.items():
         assert_close(x, v0, name)
-    # the default of so small a plan is 8 bins on the groups of 16: the widths
-    # round their taps differently
-    assert (v["16"] != v["default"]).any()
+    assert (v["16"] == v["default"]).all()
+    # groups and windows of 8 bins round their taps differently
+    assert (v["8"] != v["default"]).any()
