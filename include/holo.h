@@ -113,17 +113,23 @@ holo_status holo_workspace_bytes(const holo_plan* plan, size_t* bytes);
  * linear interpolation on the periodic H x W grid (so S_s commutes with the
  * propagators and the kernels shift Q_j = D_{rho_probe_j} q directly).
  * `shifts` is host memory [n_angles][n_dist][2], copied; NULL removes the
- * shifts.  Setting shifts grows the workspace by the frames of a chunk
- * (query holo_workspace_bytes again).  Errors: INVALID_ARGUMENT (NULL plan,
+ * shifts.  Setting shifts grows the workspace by the frames of a chunk (of
+ * joined small chunks, fewer then go together; query holo_workspace_bytes
+ * again).  Errors: INVALID_ARGUMENT (NULL plan,
  * non-finite shift).  Host-only; the device copy is refreshed by the next
  * compute call. */
 holo_status holo_plan_set_probe_shifts(holo_plan* plan, const float* shifts);
 
 /* Angles per chunk (the frames of one chunk are formed, back-propagated and
- * dropped before the next; the workspace grows with it).  Where the frames
- * of all planes are small, plans with chunks of 32 angles or more take as many
- * angles at a time as stay within 128 MB, and the workspace is sized for that
- * (it never shrinks as the chunk grows).  set_chunk changes
+ * dropped before the next; the workspace grows with it).  Where frames are
+ * small, plans with chunks of 32 angles or more take as many angles at a time
+ * as keep what is held per angle (n_dist frames and psi, OVERLAP's second
+ * psi, n_dist more frames with probe shifts) within 160 MB, if those are
+ * more: the chunk is then the least that goes together, and get_chunk returns
+ * the value that was set.  Chunks below 32 are taken as they are.  The
+ * workspace is sized for what runs (it never shrinks as the chunk grows);
+ * beside it the probe-gradient sums have up to 32 slots of n_dist frames,
+ * never more than angles that go together.  set_chunk changes
  * the plan's workspace size (query holo_workspace_bytes again); chunks below
  * the plan's largest forward angle group (at most 4 angles) are rejected
  * with INVALID_ARGUMENT; values above n_angles are clamped.  Host-only. */
@@ -132,8 +138,9 @@ holo_status holo_plan_get_chunk(const holo_plan* plan, int32_t* chunk);
 
 /* Autotuner of the chunk size: one untimed gradient, then one gradient per
  * candidate timed with HIP events on `stream` (times_ms[n_cand], may be
- * NULL); the fastest candidate becomes the plan's chunk and is returned in
- * *best_chunk.  The inputs and outputs are those of holo_grad (all
+ * NULL; candidates that take the same angles together are timed once, the
+ * first of them for all); the fastest candidate becomes the plan's chunk and
+ * is returned in *best_chunk.  The inputs and outputs are those of holo_grad (all
  * required); `ws` must hold the workspace of the largest candidate
  * (WORKSPACE_TOO_SMALL otherwise, before any device work).  Synchronises
  * `stream`.  The chunk is a launch-shape choice: results agree with any

@@ -15,6 +15,7 @@
 #include "holo_internal.hpp"
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -236,22 +237,34 @@ static void set_fwd_bins(holo_plan* P, int nb) {
   P->groups_dirty = true;
 }
 
+// Chunks of small frames go several together: a 64-angle chunk leaves the chip
+// half empty in every launch (128 px and 180 angles: 3 launches of the ray
+// sums of 69 us, or one of 97; two solver iterations 4.07 -> 3.05 ms).  The
+// bytes are what 64 angles of 4 planes take at 256 px, where a launch fills
+// the chip.  Below half the default chunk the caller's number runs, for plans
+// that have to be small: 31 angles against joined ones, one gradient of 4
+// planes and its workspace, 64 px and 360 angles 1.15 ms in 41 MB against 0.37
+// in 95, 128 px and 180 angles 1.05 in 123 against 0.49 in 221, 192 px and 300
+// angles 3.14 in 342 against 2.06 in 463.
+constexpr int kJoinChunk = 32;
+constexpr size_t kJoinBytes = (size_t)160 << 20;
+
 // Workspace layout of a plan (depends on its chunk).
 static void layout_workspace(holo_plan* P) {
   const size_t fr = (size_t)P->H * P->W * sizeof(float2);
   size_t o = 0;
   P->off_Q = o;   o = align_up(o + fr * P->nd);
-  // Angles that go through the stages together: the plan's chunk, or, from 32
-  // angles on, as many as keep the frames under 128 MB if those are more (so
-  // the workspace never shrinks as the chunk grows).  A
-  // 64-angle chunk of small frames leaves the chip half empty in every launch:
-  // at 128 px and 180 angles the ray sums took 3 launches of 69 us, and take
-  // one of 97; a five-iteration solve 4.07 -> 3.05 ms.  A caller who asks for
-  // less than 32 angles wants little memory and gets that.
+  const bool fs = P->projector == HOLO_PROJECTOR_FOURIER;
+  // the second psi buffer of the overlapped forward (Joseph's ray sums only)
+  const bool two_psi = P->overlap && !fs;
+  // Angles that go through the stages together: the plan's chunk, or, from
+  // kJoinChunk angles on, as many as keep everything held per angle (frames,
+  // psi, probe-shift products) under kJoinBytes if those are more (so the
+  // workspace never shrinks as the chunk grows).
   P->run_chunk = P->chunk;
-  if (P->chunk >= 32)
-    P->run_chunk = (int)std::min<size_t>(
-        P->n_angles, std::max<size_t>(P->chunk, ((size_t)1 << 27) / (fr * P->nd)));
+  const size_t per = fr * (P->nd + 1 + (two_psi ? 1 : 0) + (P->pshift.empty() ? 0 : P->nd));
+  if (P->chunk >= kJoinChunk)
+    P->run_chunk = (int)std::min<size_t>(P->n_angles, std::max<size_t>(P->chunk, kJoinBytes / per));
   const int chunk = P->run_chunk;
   P->c_split = pass_c_split(P->H, P->W, P->nd, chunk);
   P->off_G = o;   o = align_up(o + fr * P->nd * P->c_split);
@@ -259,13 +272,10 @@ static void layout_workspace(holo_plan* P) {
   // z-blocked copies of the volume read by the ray sums (one per walk
   // direction), rows padded by kFwdPad zero columns on each side
   // (not used by the Fourier-slice projector)
-  const size_t vb = P->projector == HOLO_PROJECTOR_FOURIER
-                        ? 0 : (size_t)P->H * P->W * vol_row(P->W) * sizeof(float2);
+  const size_t vb = fs ? 0 : (size_t)P->H * P->W * vol_row(P->W) * sizeof(float2);
   P->off_ub = o;  o = align_up(o + vb);
   P->off_uTb = o; o = align_up(o + (P->any_xwalk ? vb : 0));
   P->off_psi = o; o = align_up(o + fr * chunk);
-  // the second psi buffer of the overlapped forward (Joseph's ray sums only)
-  const bool two_psi = P->overlap && P->projector == HOLO_PROJECTOR_JOSEPH;
   P->off_psi2 = o; o = align_up(o + (two_psi ? fr * chunk : 0));
   P->off_X = o;   o = align_up(o + fr * chunk * P->nd);
   // sinogram rows carry kAdjPad zero bins on each side
@@ -284,7 +294,6 @@ static void layout_workspace(holo_plan* P) {
   // largest magnitude of every slice of the sinogram
   P->off_smax = o; o = align_up(o + (size_t)P->H * sizeof(unsigned));
   // Fourier-slice projector: the grids of one slab and its polar samples
-  const bool fs = P->projector == HOLO_PROJECTOR_FOURIER;
   const size_t M = 2 * (size_t)P->W;
   // slabs per launch: one at 512 px and above (67 MB of grids); below that as
   // many as take as much, since a single one leaves most of the chip idle
@@ -1363,12 +1372,28 @@ extern "C" holo_status holo_plan_autotune_tile(holo_plan* P, int32_t param, cons
                ws_bytes, stream);
   };
   // One untimed gradient first (device tables, code load), then one timed
-  // gradient per candidate; the fastest becomes the plan's value.
+  // gradient per candidate; the fastest becomes the plan's value.  Candidates
+  // that run alike (joined chunks, slab depths) are timed once: the first of
+  // them stands for all.
   int best = chunk0;
   float best_ms = 0.f;
+  struct Timed {
+    std::array<int, 6> shape;               // what a call of the candidate launches
+    float ms;
+  };
+  std::array<Timed, 16> seen;
+  size_t n_seen = 0;
   s = grad();
   for (int i = 0; i < n_cand && s == HOLO_OK; ++i) {
     tile_put(P, param, candidates[i]);
+    const std::array<int, 6> shape = {P->run_chunk, P->col_tile ? P->col_tile : cols_per_wg(P->H),
+                                      P->fwd_nb, P->fwd_auto, P->overlap, P->max_group};
+    const Timed* same = std::find_if(seen.data(), seen.data() + n_seen,
+                                     [&](const Timed& t) { return t.shape == shape; });
+    if (same != seen.data() + n_seen) {
+      if (times_ms) times_ms[i] = same->ms;
+      continue;
+    }
     float ms = 0.f;
     if (hipEventRecord(e0, st) != hipSuccess) { s = fail(HOLO_ERR_HIP, "hipEventRecord"); break; }
     s = grad();
@@ -1378,6 +1403,7 @@ extern "C" holo_status holo_plan_autotune_tile(holo_plan* P, int32_t param, cons
       s = fail(HOLO_ERR_HIP, "holo_plan_autotune: event timing failed");
       break;
     }
+    if (n_seen < seen.size()) seen[n_seen++] = Timed{shape, ms};
     if (times_ms) times_ms[i] = ms;
     if (i == 0 || ms < best_ms) {
       best_ms = ms;
