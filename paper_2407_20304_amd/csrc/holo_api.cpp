@@ -177,7 +177,7 @@ static void build_fs_tables(holo_plan* P) {
     while (pos < P->n_angles && tm[P->fs_sorted[pos]] < lo) ++pos;
     P->fs_bins[b] = b == kFsBins ? P->n_angles : pos;
   }
-  fs_build_items(W, P->n_angles, P->fs_items, P->fs_parts);
+  fs_build_items(W, P->n_angles, P->fs_bins, P->fs_items, P->fs_parts);
 }
 
 // Can angles [a, b) share the staged row windows of the forward ray sums?

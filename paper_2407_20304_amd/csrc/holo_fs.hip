@@ -519,24 +519,42 @@ __global__ __launch_bounds__(fs_nt(2 * W)) void k_fs_rows_T(const float2* __rest
 // Launchers
 // ---------------------------------------------------------------------------
 
-// Work items of the spread for a plan of n_angles angles: the tiles that
-// more than kSpShare lines can meet, in shares of at most that many lines,
-// then the others.  The window of a tile at distance rc holds about n_angles
-// 2 asin(d / rc) / pi lines; 128 lines keep a workgroup about as long as
-// the outer tiles of its launch take together.
+// Work items of the spread: the tiles whose angle windows hold more than
+// kSpShare of the plan's lines, in shares of at most that many, then the
+// others.  Lines are counted as the kernel finds them, images and spare bins
+// included, so that scans over part of the half-turn are shared as evenly as
+// full ones; 128 lines keep a workgroup about as long as the outer tiles of
+// its launch take together.
 constexpr int kSpShare = 128;
 
-void fs_build_items(int W, int n_angles, std::vector<FsItem>& items, int& n_parts) {
+void fs_build_items(int W, int n_angles, const std::vector<int>& bin_first, std::vector<FsItem>& items,
+                    int& n_parts) {
   const int M = 2 * W, nti = M / kSpTile;
   const double d = 8.0 * 1.4142135623730951 + 0.5 * KW * 1.4142135623730951 + 0.05;
   items.clear();
   n_parts = 0;
   std::vector<FsItem> whole;
+  // lines of an image whose centre is (cx, cy) from frequency zero
+  auto image_lines = [&](double cx, double cy) {
+    const double rc = std::sqrt(cx * cx + cy * cy);
+    if (rc > 0.5 * M + d) return 0;
+    if (rc <= d) return n_angles;
+    const double dl = std::asin(d / rc), bsc = kFsBins / M_PI;
+    double phi = std::atan2(cy, cx);
+    if (phi < 0.0) phi += M_PI;
+    if (phi >= M_PI) phi -= M_PI;
+    const int b0 = (int)std::floor((phi - dl) * bsc) - 1, b1 = (int)std::floor((phi + dl) * bsc) + 1;
+    if (b1 - b0 + 1 >= kFsBins) return n_angles;
+    if (b0 < 0) return n_angles - bin_first[b0 + kFsBins] + bin_first[b1 + 1];
+    if (b1 >= kFsBins) return n_angles - bin_first[b0] + bin_first[b1 - kFsBins + 1];
+    return bin_first[b1 + 1] - bin_first[b0];
+  };
   for (int t = 0; t < nti * nti; ++t) {
     const double cx = (t % nti) * kSpTile - M / 2 + 7.5, cy = (t / nti) * kSpTile - M / 2 + 7.5;
-    const double rc = std::sqrt(cx * cx + cy * cy);
-    const double lines = rc <= d ? n_angles : n_angles * 2.0 * std::asin(d / rc) / M_PI;
-    const int parts = (int)std::ceil(lines / kSpShare);
+    int lines = 0;
+    for (int im = 0; im < 9; ++im)
+      lines = std::max(lines, image_lines(cx + (im % 3 - 1) * M, cy + (im / 3 - 1) * M));
+    const int parts = (lines + kSpShare - 1) / kSpShare;
     if (parts <= 1) {
       whole.push_back(FsItem{t, 0, 1, 0});
       continue;

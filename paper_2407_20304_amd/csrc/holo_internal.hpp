@@ -162,7 +162,9 @@ hipError_t launch_cols_pad(const DevGeom& g, const PadJob& jb, double* Fpart, hi
 // slices.  Per slab, G: kFsSlab grids of (2W)^2; A: kFsSlab * n_angles *
 // (W + 1) polar samples; Part: n_parts partial tiles (256 points of kFsSlab).
 bool fs_size_supported(int W);
-void fs_build_items(int W, int n_angles, std::vector<FsItem>& items, int& n_parts);
+// (bin_first: the table of FsArgs)
+void fs_build_items(int W, int n_angles, const std::vector<int>& bin_first, std::vector<FsItem>& items,
+                    int& n_parts);
 hipError_t launch_fs_forward(const DevGeom& g, const FsArgs& f, const float2* u, float2* G,
                              float2* S, int z0, int nslab, hipStream_t st);
 hipError_t launch_fs_adjoint(const DevGeom& g, const FsArgs& f, const float2* S, float2* A,

@@ -34,7 +34,8 @@ EDGES = np.array([0.0, 1e-9, np.pi / 4 - 1e-6, np.pi / 4, np.pi / 4 + 1e-6, np.p
 
 # 64 px: halves in every launch; 512: in short ones; edges: axes, the walk
 # switch, windows outside the volume at either end
-@pytest.mark.parametrize("W,n", [(64, 90), (512, 70), (192, EDGES), (1024, EDGES[:7])], ids=str)
+@pytest.mark.parametrize("W,n", [(64, 90), (512, 70), (192, EDGES), (1024, EDGES[:7])],
+                         ids=["64", "512", "192-edges", "1024-edges"])
 def test_the_same_bits_in_every_chunk_and_range(W, n):
     p = _problem(W, n)
     n = len(p.geom.theta)
