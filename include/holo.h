@@ -254,10 +254,11 @@ holo_status holo_plan_set_padding(holo_plan* plan, int32_t pad);
  *     approximation error a few 1e-8 relative) with O(W^2 log W + N_theta W)
  *     work per slice instead of O(N_theta W^2).  Its transpose is the exact
  *     transpose of the same computation.  Needs det_cols <= 1024; changes
- *     the workspace (per 8 slices of a launch, grids of (2W)^2, N_theta
- *     (W + 1) samples of each and partial tiles, for up to 64 MB of grids, in
- *     place of the ray sums' slice-blocked volume copies; query
- *     holo_workspace_bytes again).
+ *     the workspace (in place of the ray sums' slice-blocked volume copies,
+ *     for every 8 slices of a launch 8 grids of (2W)^2, 8 N_theta (W + 1)
+ *     samples and partial tiles: as many slices as keep the grids within 64
+ *     MB and all of it within 384 MB, at least 8, whose grids take 67 MB at
+ *     512 columns and 268 at 1024; query holo_workspace_bytes again).
  * Errors: INVALID_ARGUMENT (NULL plan, unknown value), UNSUPPORTED_SIZE
  * (FOURIER with det_cols above 1024).  Host-only. */
 typedef enum {

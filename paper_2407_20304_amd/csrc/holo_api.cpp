@@ -248,6 +248,8 @@ static void set_fwd_bins(holo_plan* P, int nb) {
 // angles 3.14 in 342 against 2.06 in 463.
 constexpr int kJoinChunk = 32;
 constexpr size_t kJoinBytes = (size_t)160 << 20;
+// Most that several slabs of the Fourier-slice projector may take together.
+constexpr size_t kFsBytes = (size_t)384 << 20;
 
 // Workspace layout of a plan (depends on its chunk).
 static void layout_workspace(holo_plan* P) {
@@ -293,20 +295,23 @@ static void layout_workspace(holo_plan* P) {
   P->off_Pbuf = o; o = align_up(o + (P->pshift.empty() ? 0 : fr * chunk * P->nd));
   // largest magnitude of every slice of the sinogram
   P->off_smax = o; o = align_up(o + (size_t)P->H * sizeof(unsigned));
-  // Fourier-slice projector: the grids of one slab and its polar samples
+  // Fourier-slice projector, per slab: its grids, polar samples of every angle
+  // and partial tiles.  Slabs per launch: one where its grids take 64 MB or
+  // more (512 px: 67 MB, 1024 px: 268), below that as many as take as much,
+  // since a single one leaves most of the chip idle (128 px: 128 workgroups of
+  // 128 threads in a row pass), and no more than kFsBytes hold with samples and
+  // tiles, which grow with the angles (128 px, 720 angles: 16 slabs in 266 MB
+  // 2.28 ms a gradient, 9 and 7 in 150 MB 2.41).
   const size_t M = 2 * (size_t)P->W;
-  // slabs per launch: one at 512 px and above (67 MB of grids); below that as
-  // many as take as much, since a single one leaves most of the chip idle
-  // (128 px: 128 workgroups of 128 threads in a row pass)
   const size_t gb = (size_t)kFsSlab * M * M * sizeof(float2);
+  const size_t ab = (size_t)kFsSlab * P->n_angles * (P->W + 1) * sizeof(float2);
+  const size_t pb = (size_t)P->fs_parts * 256 * kFsSlab * sizeof(float2);
   P->fs_batch = (int)std::max<size_t>(
-      1, std::min<size_t>((size_t)P->H / kFsSlab, ((size_t)1 << 26) / gb));
+      1, std::min({(size_t)P->H / kFsSlab, ((size_t)1 << 26) / gb, kFsBytes / (gb + ab + pb)}));
   const size_t nb = fs ? (size_t)P->fs_batch : 0;
   P->off_fsG = o; o = align_up(o + nb * gb);
-  P->off_fsA = o;
-  o = align_up(o + nb * kFsSlab * P->n_angles * (P->W + 1) * sizeof(float2));
-  P->off_fsP = o;
-  o = align_up(o + nb * P->fs_parts * 256 * kFsSlab * sizeof(float2));
+  P->off_fsA = o; o = align_up(o + nb * ab);
+  P->off_fsP = o; o = align_up(o + nb * pb);
   P->ws_bytes = o;
 }
 
