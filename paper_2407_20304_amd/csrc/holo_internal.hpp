@@ -198,6 +198,13 @@ hipError_t launch_pass_d(const DevGeom& g, const float2* X, const float2* psi, f
 hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uTb, float2* psi,
                             const double* ang, const int2* groups, int g0, int ngroups, int c0,
                             int c1, int nb, bool by_size, hipStream_t st);
+// Workgroups of the split of n items of the sinogram, which walk them in
+// strides: a launch may not have 2^32 threads in a dimension, and a sinogram
+// of 128 GB has that many items.
+inline unsigned split_sino_blocks(size_t n) {
+  const size_t b = (n + kThreads - 1) / kThreads;
+  return (unsigned)(b < ((size_t)1 << 22) ? b : (size_t)1 << 22);
+}
 // Transpose of the ray sums over angles k0 .. k0 + K - 1: S holds their
 // sinogram in pass D's blocked layout (overwritten by its split form), ang
 // the plan's whole angle table, smax the slices' largest magnitudes.

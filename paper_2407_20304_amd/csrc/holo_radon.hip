@@ -417,28 +417,28 @@ __device__ __forceinline__ unsigned pack_half2(_Float16 a, _Float16 b) {
 __global__ __launch_bounds__(kThreads) void k_split_sino(unsigned* __restrict__ S,
                                                          const unsigned* __restrict__ smax,
                                                          size_t n, int Wp, int nzb) {
-  // thread: 4 consecutive slices of one bin
-  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  const size_t half = (size_t)8 * Wp * 2;            // threads per half block
-  const size_t blk = i / half, o = i % half;         // (k, z / 64), offset in it
-  const int z = (int)(blk % nzb) * kAdjZT + (int)(o / (2 * Wp)) * 8 + (int)(o & 1) * 4;
-  float4* lo = reinterpret_cast<float4*>(S) + blk * 2 * half + o;
-  float4* hi = lo + half;
-  const float4 re = *lo, im = *hi;
-  const float x[4] = {re.x, re.y, re.z, re.w}, y[4] = {im.x, im.y, im.z, im.w};
-  unsigned a[4], b[4];
+  // item: 4 consecutive slices of one bin
+  for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads) {
+    const size_t half = (size_t)8 * Wp * 2;            // items per half block
+    const size_t blk = i / half, o = i % half;         // (k, z / 64), offset in it
+    const int z = (int)(blk % nzb) * kAdjZT + (int)(o / (2 * Wp)) * 8 + (int)(o & 1) * 4;
+    float4* lo = reinterpret_cast<float4*>(S) + blk * 2 * half + o;
+    float4* hi = lo + half;
+    const float4 re = *lo, im = *hi;
+    const float x[4] = {re.x, re.y, re.z, re.w}, y[4] = {im.x, im.y, im.z, im.w};
+    unsigned a[4], b[4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const float sc = ldexpf(1.0f, split_exponent(smax[z + c]));
-    const float u = x[c] * sc, v = y[c] * sc;
-    const _Float16 u1 = (_Float16)u, v1 = (_Float16)v;
-    a[c] = pack_half2(u1, v1);
-    constexpr float tail = (float)(1 << kAdjTail);
-    b[c] = pack_half2((_Float16)((u - (float)u1) * tail), (_Float16)((v - (float)v1) * tail));
+    for (int c = 0; c < 4; ++c) {
+      const float sc = ldexpf(1.0f, split_exponent(smax[z + c]));
+      const float u = x[c] * sc, v = y[c] * sc;
+      const _Float16 u1 = (_Float16)u, v1 = (_Float16)v;
+      a[c] = pack_half2(u1, v1);
+      constexpr float tail = (float)(1 << kAdjTail);
+      b[c] = pack_half2((_Float16)((u - (float)u1) * tail), (_Float16)((v - (float)v1) * tail));
+    }
+    *reinterpret_cast<uint4*>(lo) = make_uint4(a[0], a[1], a[2], a[3]);
+    *reinterpret_cast<uint4*>(hi) = make_uint4(b[0], b[1], b[2], b[3]);
   }
-  *reinterpret_cast<uint4*>(lo) = make_uint4(a[0], a[1], a[2], a[3]);
-  *reinterpret_cast<uint4*>(hi) = make_uint4(b[0], b[1], b[2], b[3]);
 }
 
 // Per-angle constants of a tile: fractional bin of its corner voxel relative
@@ -774,7 +774,7 @@ hipError_t launch_radon_adj(const DevGeom& g, float2* S, float2* gu, const doubl
   unsigned* Sw = reinterpret_cast<unsigned*>(S);
   const int Wp = sino_row(g.W), nzb = g.H / kAdjZT;
   const size_t ns = (size_t)K * nzb * Wp * 16;
-  k_split_sino<<<(unsigned)((ns + kThreads - 1) / kThreads), kThreads, 0, st>>>(Sw, smax, ns, Wp, nzb);
+  k_split_sino<<<split_sino_blocks(ns), kThreads, 0, st>>>(Sw, smax, ns, Wp, nzb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const unsigned n = (unsigned)(g.W / 16) * (unsigned)(g.W / 16) * (unsigned)nzb;
