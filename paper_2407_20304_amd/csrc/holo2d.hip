@@ -31,17 +31,25 @@ __host__ __device__ constexpr int b_rows_tl(int n) { return fft_row_threads(n); 
 __host__ __device__ constexpr int b_rows_lpw(int n) { return kT2 / fft_row_threads(n); }
 // Columns per column-pass workgroup: 8 from 384 on, so that the tile of a
 // batch whose instances are at most 512 px fits 37 KB of LDS (four
-// workgroups per CU instead of two).
-__host__ __device__ constexpr int b_cols_tc(int n) { return n >= 384 ? 8 : 16; }
+// workgroups per CU instead of two).  Whole frames of 64 px in batches that
+// fill the chip (`wide`, see b2_wide): 8 elements per thread, so that the
+// radix-8 stages occupy all of them; with 16 columns it is 2, and 200 problems
+// of 4 planes took 55 us a launch (38 with 256 threads) and 216 us a call
+// against 160 now.
+__host__ __device__ constexpr int b_cols_tc(int n, bool wide = false) {
+  return n >= 384 ? 8 : wide && n == 64 ? 64 : 16;
+}
 // Pitch of one column line of a tile of tc columns: at least the padded line,
 // and an odd multiple of 32 / tc.  32 consecutive threads then read or write
 // tc columns times 32 / tc rows of the tile in distinct banks (8 bytes each).
+// Tiles of 64 columns: odd for the same reason, and 5 past a multiple of 32,
+// which halves the conflicts of 4 lines of 8 threads in the transforms.
 __host__ __device__ constexpr int b_col_pitch(int n, int tc) {
-  return (fft_line_len(n) - 32 / tc + 64 / tc - 1) / (64 / tc) * (64 / tc) + 32 / tc;
+  return tc > 32 ? fft_line_len(n) + 3 : (fft_line_len(n) - 32 / tc + 64 / tc - 1) / (64 / tc) * (64 / tc) + 32 / tc;
 }
 // LDS of one column workgroup of size n: twiddles plus the tile.
-__host__ __device__ constexpr int b_cols_lds(int n) {
-  return fft_line_len(n) + b_cols_tc(n) * b_col_pitch(n, b_cols_tc(n));
+__host__ __device__ constexpr int b_cols_lds(int n, bool wide = false) {
+  return fft_line_len(n) + b_cols_tc(n, wide) * b_col_pitch(n, b_cols_tc(n, wide));
 }
 
 // The probe-gradient column pass keeps every plane's spectrum sum in
@@ -53,7 +61,7 @@ __host__ __device__ constexpr int b_gq_lds(int n) {
 }
 
 int b2_rows_per_wg(int n) { return b_rows_lpw(n); }
-int b2_cols_per_wg(int n) { return b_cols_tc(n); }
+int b2_cols_per_wg(int n, bool wide) { return b_cols_tc(n, wide); }
 int b2_gq_per_wg(int n) { return b_gq_tc(n); }
 bool b2_size_supported(int n) {
   switch (n) {
@@ -67,10 +75,10 @@ constexpr int kRowLds = 1024 + 3072;          // float2 elements
 // column-kernel LDS (float2) for batches up to 512 px and with 1024 px
 constexpr int kColLdsSmall = b_cols_lds(512), kColLdsLarge = b_cols_lds(1024);
 static_assert(b_col_pitch(512, 8) == 532 && b_col_pitch(384, 8) == 396 && b_col_pitch(256, 16) == 266 &&
-                  b_col_pitch(512, 4) == 536, "bank spread");
+                  b_col_pitch(512, 4) == 536 && b_col_pitch(64, 64) == 69, "bank spread");
 static_assert(b_cols_lds(384) <= kColLdsSmall && b_cols_lds(256) <= kColLdsSmall &&
                   b_cols_lds(192) <= kColLdsSmall && b_cols_lds(128) <= kColLdsSmall &&
-                  b_cols_lds(64) <= kColLdsSmall,
+                  b_cols_lds(64) <= kColLdsSmall && b_cols_lds(64, true) <= kColLdsSmall,
               "small column LDS covers every size up to 512");
 
 __device__ __forceinline__ double b_src_pos(double c, double m, int idx) {
@@ -325,9 +333,9 @@ __device__ __forceinline__ void b_block_sum(double v, double* out) {
   if (threadIdx.x == 0) *out = red[0];
 }
 
-template <int N>
+template <int N, bool WIDE = false>
 __device__ __forceinline__ void b_cols_body(const B2Args& A, const B2Item& it, float2* lds) {
-  constexpr int TC = b_cols_tc(N), TLc = kC2 / TC;
+  constexpr int TC = b_cols_tc(N, WIDE), TLc = kC2 / TC;
   float2* s_tw = lds;
   const int cidx = threadIdx.x / TLc, lt = threadIdx.x % TLc;
   // column lines stored padded (element zz at fpi(zz)), pitch b_col_pitch
@@ -448,7 +456,13 @@ __global__ __launch_bounds__(kC2) __attribute__((amdgpu_waves_per_eu(LDS == kCol
   case N:       \
     if constexpr (b_cols_lds(N) <= LDS) b_cols_body<N>(A, it, lds); \
     break;
-    CASE(64) CASE(128) CASE(192) CASE(256) CASE(384) CASE(512) CASE(1024)
+    case 64:
+      if (A.wide)
+        b_cols_body<64, true>(A, it, lds);
+      else
+        b_cols_body<64>(A, it, lds);
+      break;
+    CASE(128) CASE(192) CASE(256) CASE(384) CASE(512) CASE(1024)
 #undef CASE
     default: break;
   }

@@ -21,6 +21,17 @@ namespace {
 
 constexpr int kProbeGroups = 512;
 
+// Should the column passes take 64-px frames whole?  From more than one
+// workgroup per CU in pass B on; below, workgroups of 16 columns leave fewer
+// CUs idle.  16 problems of 4 planes (256 workgroups of 16 columns) 50.9 us a
+// call and 53.4 with whole frames, 24 57.2 and 54.2; 48 of one plane 42.6 and
+// 45.0, 96 54.7 and 51.7.
+bool b2_wide(const int32_t* sizes, int n_inst, int nd) {
+  long long wgs = 0;
+  for (int i = 0; i < n_inst; ++i) wgs += sizes[i] / b2_cols_per_wg(sizes[i], false) * nd;
+  return wgs > 256;
+}
+
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct ItemList {
@@ -36,6 +47,7 @@ struct holo2d_plan {
   double m0 = 0, fresnel0 = 0;
   std::vector<double> mag;
   unsigned unit = 0;                      // planes of magnification 1 (bit j)
+  bool wide = false;                      // 64-px frames in one column workgroup each
   std::vector<int> sizes;
   std::vector<long long> off;
   long long total = 0;
@@ -166,11 +178,12 @@ extern "C" holo_status holo2d_plan_create(int32_t n_inst, const int32_t* sizes, 
     std::stable_sort(order.begin(), order.end(),
                      [&](int a, int b) { return P->sizes[a] > P->sizes[b]; });
     P->ranges.assign(n_inst, make_int2(0, 0));
+    P->wide = b2_wide(sizes, n_inst, n_dist);
     std::vector<int> slot_base(n_inst);
     int slots = 0;
     for (int i = 0; i < n_inst; ++i) {
       const int n = P->sizes[i];
-      const int per = n / b2_cols_per_wg(n);
+      const int per = n / b2_cols_per_wg(n, P->wide);
       slot_base[i] = slots;
       P->ranges[i] = make_int2(slots, slots + per * (n_dist + 1));
       slots += per * (n_dist + 1);
@@ -186,7 +199,7 @@ extern "C" holo_status holo2d_plan_create(int32_t n_inst, const int32_t* sizes, 
         1, std::min<long long>(n_dist + 1, wgs * (n_dist + 1) / kProbeGroups));
     for (int i : order) {
       const int n = P->sizes[i];
-      const int lpw = b2_rows_per_wg(n), tc = b2_cols_per_wg(n);
+      const int lpw = b2_rows_per_wg(n), tc = b2_cols_per_wg(n, P->wide);
       // job n_dist of the probe and pass-C rows is the reference term
       for (int j = 0; j <= n_dist; ++j)
         for (int z = 0; z < n; z += lpw) {
@@ -372,6 +385,7 @@ holo_status b2_launch(holo2d_plan* P, B2Run run, const char* tb, char* w, const 
   A.nd = P->nd;
   A.functional = P->functional == HOLO_FUNCTIONAL_INTENSITY ? 1 : 0;
   A.max_n = P->dsizes.back();
+  A.wide = P->wide ? 1 : 0;
   A.unit = P->unit;
   A.ident = conv ? 0 : P->unit;   // rho_probe_j = 0
   for (int j = 0; j < P->nd; ++j) A.mag[j] = P->mag[j];

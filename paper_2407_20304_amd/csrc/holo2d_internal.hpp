@@ -50,6 +50,7 @@ struct B2Args {
   int want_gq;             // the probe gradient is wanted (and the reference term with it)
   int functional;          // 0: amplitude (F2), 1: intensity (F1)
   int max_n;               // largest instance size of the batch
+  int wide;                // 64-px frames in one column workgroup each
   unsigned unit;           // planes of magnification 1: B_j is the identity
   unsigned ident;          // planes whose Q_j is q itself (D_{rho_probe_j} = 1)
   double mag[8];
@@ -70,7 +71,7 @@ struct B2Args {
 constexpr int kGatherRows = 8;   // rows (of 64 columns) of one gather item
 
 int b2_rows_per_wg(int n);
-int b2_cols_per_wg(int n);
+int b2_cols_per_wg(int n, bool wide);
 int b2_gq_per_wg(int n);
 bool b2_size_supported(int n);
 
