@@ -10,6 +10,7 @@
 //   radon_adj     transpose as products on the matrix cores (a workgroup per
 //                 16 x 16 voxel tile and 64 slices, all angles), sinogram
 //                 segments staged in LDS per angle group by LDS-direct loads
+//   radon_adj_few the same over up to four angles, without the split pass
 // None is bound by HBM: every voxel is revisited once per angle.
 #include <algorithm>
 
@@ -406,6 +407,26 @@ __device__ __forceinline__ unsigned pack_half2(_Float16 a, _Float16 b) {
   return __builtin_bit_cast(unsigned, v);
 }
 
+// Four slices of one bin (real parts x, imaginary parts y, bits of the slices'
+// largest magnitudes m) as first and second terms.
+struct SplitTerms {
+  uint4 first, second;
+};
+__device__ __forceinline__ SplitTerms split_samples(float4 re, float4 im, const unsigned* m) {
+  const float x[4] = {re.x, re.y, re.z, re.w}, y[4] = {im.x, im.y, im.z, im.w};
+  unsigned a[4], b[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float sc = ldexpf(1.0f, split_exponent(m[c]));
+    const float u = x[c] * sc, v = y[c] * sc;
+    const _Float16 u1 = (_Float16)u, v1 = (_Float16)v;
+    a[c] = pack_half2(u1, v1);
+    constexpr float tail = (float)(1 << kAdjTail);
+    b[c] = pack_half2((_Float16)((u - (float)u1) * tail), (_Float16)((v - (float)v1) * tail));
+  }
+  return SplitTerms{make_uint4(a[0], a[1], a[2], a[3]), make_uint4(b[0], b[1], b[2], b[3])};
+}
+
 // The sinogram as pass D leaves it to the split form that k_radon_adj stages,
 // in the same memory.  Both are [k][z / 64][2][(z / 8) % 8][bin][z % 8]
 // words of 32 bits: pass D puts the real part in half 0 and the imaginary
@@ -424,20 +445,9 @@ __global__ __launch_bounds__(kThreads) void k_split_sino(unsigned* __restrict__ 
     const int z = (int)(blk % nzb) * kAdjZT + (int)(o / (2 * Wp)) * 8 + (int)(o & 1) * 4;
     float4* lo = reinterpret_cast<float4*>(S) + blk * 2 * half + o;
     float4* hi = lo + half;
-    const float4 re = *lo, im = *hi;
-    const float x[4] = {re.x, re.y, re.z, re.w}, y[4] = {im.x, im.y, im.z, im.w};
-    unsigned a[4], b[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float sc = ldexpf(1.0f, split_exponent(smax[z + c]));
-      const float u = x[c] * sc, v = y[c] * sc;
-      const _Float16 u1 = (_Float16)u, v1 = (_Float16)v;
-      a[c] = pack_half2(u1, v1);
-      constexpr float tail = (float)(1 << kAdjTail);
-      b[c] = pack_half2((_Float16)((u - (float)u1) * tail), (_Float16)((v - (float)v1) * tail));
-    }
-    *reinterpret_cast<uint4*>(lo) = make_uint4(a[0], a[1], a[2], a[3]);
-    *reinterpret_cast<uint4*>(hi) = make_uint4(b[0], b[1], b[2], b[3]);
+    const SplitTerms t = split_samples(*lo, *hi, smax + z);
+    *reinterpret_cast<uint4*>(lo) = t.first;
+    *reinterpret_cast<uint4*>(hi) = t.second;
   }
 }
 
@@ -450,6 +460,98 @@ struct AdjAngle {
   float ih, ih2;
   int bin0, row;
 };
+
+// The first staged bin is the tile's lowest projection, moved into
+// [-kAdjPad, W + kAdjPad - kAdjBins] (a segment outside that range lies wholly
+// off the detector, and the padding it is moved to holds zeros); so are those
+// of angles that are not `live`, with weight 0.  Double precision; (X0, Y0):
+// the tile's corner from the grid's centre.
+__device__ __forceinline__ AdjAngle adj_angle(const double* ap, bool live, double cW, double X0,
+                                              double Y0, int W, int row) {
+  const double C = ap[kCos], Sn = ap[kSin], ih = live ? ap[kInvH] : 0.0;
+  const double q0 = cW + X0 * C + Y0 * Sn;
+  int sl = (int)floor(q0 + 15.0 * fmin(C, 0.0) + 15.0 * fmin(Sn, 0.0));
+  sl = live ? min(max(sl, -kAdjPad), W + kAdjPad - kAdjBins) : -kAdjPad;
+  AdjAngle a;
+  a.f0 = (float)(q0 - (double)sl);
+  a.c = (float)C;
+  a.s = (float)Sn;
+  a.mn = (float)(3.0 * fmin(C, 0.0) + 3.0 * fmin(Sn, 0.0));
+  const double ws = (double)(1 << kAdjWScale);
+  a.ih = (float)(ih * ws);
+  a.ih2 = (float)(ih * ih * ws);
+  a.bin0 = sl + kAdjPad;
+  a.row = row;
+  return a;
+}
+
+// Tile of workgroup L (see k_radon_adj): corner and slice block.
+struct AdjTile {
+  int x0, y0, zb;
+};
+__device__ __forceinline__ AdjTile adj_tile(int L, int W) {
+  const int nt = W / 16;
+  const int GS = (nt % 8 == 0) ? 8 : (nt % 4 == 0) ? 4 : (nt % 2 == 0) ? 2 : 1;
+  const int tl = L % (nt * nt), grp = tl / (GS * GS), in_grp = tl % (GS * GS);
+  return AdjTile{((grp % (nt / GS)) * GS + in_grp % GS) * 16,
+                 ((grp / (nt / GS)) * GS + in_grp / GS) * 16, L / (nt * nt)};
+}
+
+// A lane's operands of one 4 x 4 block at one angle: its 8 weights as first
+// terms, second terms and first terms times 2^-kAdjTail, and the block's first
+// bin.  (fbx, fby): the block's first voxel, (vx, vy): the lane's.
+struct AdjWeights {
+  half8 w1, w2, wt;
+  int bin;
+};
+__device__ __forceinline__ AdjWeights adj_weights(AdjAngle A, float fbx, float fby, float vx,
+                                                  float vy, float minus1) {
+  AdjWeights o;
+  // the block's lowest bin, and the voxel's position above it
+  const float low = fmaf(fby, A.s, fmaf(fbx, A.c, A.f0) + A.mn);
+  const float jf = fminf(fmaxf(floorf(low), 0.f), (float)(kAdjBins - 8));
+  const float d = fmaf(vy, A.s, fmaf(vx, A.c, A.f0)) - jf;
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    const float u = fmaxf(0.0f, fmaf(-fabsf(d - (float)i), A.ih2, A.ih));
+    const float v = fmaxf(0.0f, fmaf(-fabsf(d - (float)(i + 1)), A.ih2, A.ih));
+    // one packed conversion, whose halves the remainders are then taken from
+    unsigned pu = pack_half2((_Float16)u, (_Float16)v);
+    asm volatile("" : "+v"(pu));
+    const half2v p = __builtin_bit_cast(half2v, pu);
+    const half2v r = {(_Float16)fmaf((float)p[0], minus1, u), (_Float16)fmaf((float)p[1], minus1, v)};
+    const half2v t = p * (half2v)((_Float16)(1.0f / (1 << kAdjTail)));
+    o.w1[i] = p[0];
+    o.w1[i + 1] = p[1];
+    o.w2[i] = r[0];
+    o.w2[i + 1] = r[1];
+    o.wt[i] = t[0];
+    o.wt[i + 1] = t[1];
+  }
+  o.bin = (int)jf;
+  return o;
+}
+
+// Store of one 16-column tile of a block's result: the lane holds column m
+// (slice z, re or im) of rows 4 ga .. 4 ga + 3, which are the four voxels from
+// `row` on.  Lanes m and m ^ 1 exchange halves, so each stores two complex
+// voxels.
+__device__ __forceinline__ void adj_store(float4v r, const unsigned* smax, int z, bool im, float2* row) {
+  const float sc = ldexpf(1.0f, -split_exponent(smax[z]) - kAdjWScale);
+  const float4v v = r * sc;
+  const float s0 = im ? v[0] : v[2], s1 = im ? v[1] : v[3];
+  const float r0 = __shfl_xor(s0, 1, 64), r1 = __shfl_xor(s1, 1, 64);
+  const float4 o = im ? make_float4(r0, v[2], r1, v[3]) : make_float4(v[0], r0, v[1], r1);
+  *reinterpret_cast<float4*>(row + (im ? 2 : 0)) = o;
+}
+
+// 8 bins of one column from two transposing LDS reads (o: in 8 bytes from wp).
+typedef __attribute__((address_space(3))) short4v* LdsHalf4;
+__device__ __forceinline__ half8 adj_read8(LdsHalf4 wp, int o) {
+  const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(wp + o);
+  const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(wp + o + 32);
+  return __builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 
 // A workgroup of 8 waves owns 16 x 16 voxels and 64 slices; wave w the two
 // 4 x 4 blocks at x = 4 (w % 4), y = 8 (w / 4) and y + 4.  It walks the
@@ -487,12 +589,8 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
   // workgroups resident on one XCD cover a compact patch of the slice block
   // whose sinogram segments, per angle, are few and stay in that XCD's L2
   const int L = xcd_logical(blockIdx.x, gridDim.x);
-  const int nt = W / 16;
-  const int GS = (nt % 8 == 0) ? 8 : (nt % 4 == 0) ? 4 : (nt % 2 == 0) ? 2 : 1;
-  const int tl = L % (nt * nt), grp = tl / (GS * GS), in_grp = tl % (GS * GS);
-  const int x0 = ((grp % (nt / GS)) * GS + in_grp % GS) * 16;
-  const int y0 = ((grp / (nt / GS)) * GS + in_grp / GS) * 16;
-  const int zb = L / (nt * nt), nzb = H / kAdjZT;
+  const AdjTile tile = adj_tile(L, W);
+  const int x0 = tile.x0, y0 = tile.y0, zb = tile.zb, nzb = H / kAdjZT;
   const size_t angw = (size_t)nzb * Wp * 128;       // words per angle
   // this workgroup's share of the angle groups (of gridDim.y), whose sums go
   // to a volume of their own
@@ -508,32 +606,13 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
   const double X0 = (double)x0 - g.cW, Y0 = (double)y0 - g.cW;
   const int ng = (K + NA - 1) / NA;
 
-  // Constants of angles [w TW, (w + 1) TW) by threads t < TW, in double
-  // precision.  The first staged bin is the tile's lowest projection, moved
-  // into [-kAdjPad, W + kAdjPad - NB] (a segment outside that range lies
-  // wholly off the detector, and the padding it is moved to holds zeros); so
-  // are those of the angles past the last, with weight 0.
+  // Constants of angles [w TW, (w + 1) TW) by threads t < TW; those past the
+  // last are not live.
   auto setup_window = [&](int w) {
     const int t = threadIdx.x;
     if (t < TW) {
       const int ka = min(w * TW + t, K - 1);
-      const bool live = w * TW + t < K;
-      const double* ap = ang + (size_t)(k0 + ka) * kAngleStride;
-      const double C = ap[kCos], Sn = ap[kSin], ih = live ? ap[kInvH] : 0.0;
-      const double q0 = g.cW + X0 * C + Y0 * Sn;
-      int sl = (int)floor(q0 + 15.0 * fmin(C, 0.0) + 15.0 * fmin(Sn, 0.0));
-      sl = live ? min(max(sl, -kAdjPad), W + kAdjPad - NB) : -kAdjPad;
-      AdjAngle a;
-      a.f0 = (float)(q0 - (double)sl);
-      a.c = (float)C;
-      a.s = (float)Sn;
-      a.mn = (float)(3.0 * fmin(C, 0.0) + 3.0 * fmin(Sn, 0.0));
-      const double ws = (double)(1 << kAdjWScale);
-      a.ih = (float)(ih * ws);
-      a.ih2 = (float)(ih * ih * ws);
-      a.bin0 = sl + kAdjPad;
-      a.row = ka;
-      s_ang[w & 1][t] = a;
+      s_ang[w & 1][t] = adj_angle(ang + (size_t)(k0 + ka) * kAngleStride, w * TW + t < K, g.cW, X0, Y0, W, ka);
     }
   };
 
@@ -593,38 +672,17 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
 #pragma unroll
     for (int t = 0; t < NT; ++t) { acc[b][t] = (float4v)(0.f); out[b][t] = (float4v)(0.f); }
 
-  // Operands of block b of group gi: the lane's 8 weights, and the LDS
-  // address of its words of the block's first pair.
-  half8 a1, a2, at;                                 // w1, w2, w1 2^-kAdjTail
+  // Operands of block b of group gi, and the LDS address of the lane's words
+  // of the block's first pair.
+  AdjWeights aw;
   unsigned bp;
   const unsigned lp = lds0 + (unsigned)((ga >> 1) * (ROWS * 32) + (m >> 2) * 64 + (ga & 1) * 32 + (m & 3) * 8);
   float minus1 = -1.0f;
-  asm volatile("" : "+s"(minus1));                  // (keeps the mixed-precision FMA below)
+  asm volatile("" : "+s"(minus1));                  // (keeps the mixed-precision FMA of the remainders)
   auto weights = [&](int gi, int b, unsigned buf) {
     const int p0 = gi * NA;
-    const AdjAngle A = s_ang[(p0 / TW) & 1][p0 % TW + ga];
-    // the block's lowest bin, and the voxel's position above it
-    const float low = fmaf(fby + 4.f * b, A.s, fmaf(fbx, A.c, A.f0) + A.mn);
-    const float jf = fminf(fmaxf(floorf(low), 0.f), (float)(NB - 8));
-    const float d = fmaf(vy + 4.f * b, A.s, fmaf(vx, A.c, A.f0)) - jf;
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-      const float u = fmaxf(0.0f, fmaf(-fabsf(d - (float)i), A.ih2, A.ih));
-      const float v = fmaxf(0.0f, fmaf(-fabsf(d - (float)(i + 1)), A.ih2, A.ih));
-      // one packed conversion, whose halves the remainders are then taken from
-      unsigned pu = pack_half2((_Float16)u, (_Float16)v);
-      asm volatile("" : "+v"(pu));
-      const half2v p = __builtin_bit_cast(half2v, pu);
-      const half2v r = {(_Float16)fmaf((float)p[0], minus1, u), (_Float16)fmaf((float)p[1], minus1, v)};
-      const half2v t = p * (half2v)((_Float16)(1.0f / (1 << kAdjTail)));
-      a1[i] = p[0];
-      a1[i + 1] = p[1];
-      at[i] = t[0];
-      at[i + 1] = t[1];
-      a2[i] = r[0];
-      a2[i + 1] = r[1];
-    }
-    bp = lp + buf + 64u * (unsigned)(int)jf;
+    aw = adj_weights(s_ang[(p0 / TW) & 1][p0 % TW + ga], fbx, fby + 4.f * b, vx, vy + 4.f * b, minus1);
+    bp = lp + buf + 64u * (unsigned)aw.bin;
   };
 
   constexpr int GPW = TW / NA;                      // groups per set-up window
@@ -660,17 +718,12 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
       // multiplied, and the next block's weights are formed between the
       // products.
       constexpr int LA = 2;
-      const half8 w1 = a1, w2 = a2, wt = at;
-      auto* wp = (__attribute__((address_space(3))) short4v*)(uintptr_t)bp;
+      const half8 w1 = aw.w1, w2 = aw.w2, wt = aw.wt;
+      const LdsHalf4 wp = (LdsHalf4)(uintptr_t)bp;
       half8 h1[NT], h2[NT];
-      auto read8 = [&](int o) {                      // o: in 8 bytes; 8 bins of a column
-        const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(wp + o);
-        const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(wp + o + 32);
-        return __builtin_bit_cast(half8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-      };
       auto fetch = [&](int t) {
-        h1[t] = read8((2 * t) * NB * 8);
-        h2[t] = read8((2 * t + 1) * NB * 8);
+        h1[t] = adj_read8(wp, (2 * t) * NB * 8);
+        h2[t] = adj_read8(wp, (2 * t + 1) * NB * 8);
       };
 #pragma unroll
       for (int t = 0; t < LA; ++t) fetch(t);
@@ -693,7 +746,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
       }
     }
     // (formed above, not sunk below the branch)
-    asm volatile("" : "+v"(a1), "+v"(a2), "+v"(at), "+v"(bp));
+    asm volatile("" : "+v"(aw.w1), "+v"(aw.w2), "+v"(aw.wt), "+v"(bp));
     const unsigned next = buf0;
     buf0 = buf1;
     buf1 = buf2;
@@ -708,24 +761,81 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __
   }
   // no load may arrive in LDS after the workgroup has ended
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  // result layout: lane holds column n = m (slice 8 t + n / 2, re or im) of
-  // rows 4 ga .. 4 ga + 3: voxels bx .. bx + 3 of the block's row ga.  Lanes
-  // n and n ^ 1 exchange halves, so each stores two complex voxels.
+  // tile t of block b: column m is slice 8 t + m / 2, row ga of the block
   const size_t WW = (size_t)W * W;
-  const bool im = (m & 1) != 0;
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int z = zb * kAdjZT + 8 * t + (m >> 1);
-      const float sc = ldexpf(1.0f, -split_exponent(smax[z]) - kAdjWScale);
-      const float4v v = out[b][t] * sc;
-      const float s0 = im ? v[0] : v[2], s1 = im ? v[1] : v[3];
-      const float r0 = __shfl_xor(s0, 1, 64), r1 = __shfl_xor(s1, 1, 64);
-      const float4 o = im ? make_float4(r0, v[2], r1, v[3]) : make_float4(v[0], r0, v[1], r1);
-      float2* dst = gu + (size_t)z * WW + (size_t)(y0 + by + 4 * b + ga) * W + x0 + bx + (im ? 2 : 0);
-      *reinterpret_cast<float4*>(dst) = o;
+      adj_store(out[b][t], smax, z, (m & 1) != 0,
+                gu + (size_t)z * WW + (size_t)(y0 + by + 4 * b + ga) * W + x0 + bx);
     }
+}
+
+// The same for a single group (up to 4 angles), from the sinogram as pass D
+// leaves it: nothing to pipeline, so the samples are split on their way into
+// one LDS buffer, and two workgroups per CU hide each other's reads and the
+// stores, which bound it.  One angle, against the general kernel and its split
+// pass: 64^3 14.6 -> 9.8 us, 256^3 51.5 -> 34.8, 1024^3 2.40 -> 1.80 ms (8.6
+// GB written).
+__global__ __launch_bounds__(kAdjThreads, 4) void k_radon_adj_few(const float* __restrict__ S,
+                                                                  float2* __restrict__ gu, DevGeom g,
+                                                                  const double* __restrict__ ang,
+                                                                  int k0, int K,
+                                                                  const unsigned* __restrict__ smax) {
+  constexpr int NA = 4, NB = kAdjBins, NT = kAdjZT / 8, ROWS = 2 * NT * 2 * NB;
+  __shared__ uint4 tile4[ROWS * 4];                 // the layout of k_radon_adj's buffers
+  __shared__ AdjAngle s_ang[NA];
+  const int W = g.W, Wp = sino_row(W), nzb = g.H / kAdjZT;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const AdjTile tile = adj_tile(xcd_logical(blockIdx.x, gridDim.x), W);
+  const size_t angw = (size_t)nzb * Wp * 128;       // words per angle
+  if (threadIdx.x < NA) {
+    const int ka = min((int)threadIdx.x, K - 1);
+    s_ang[threadIdx.x] = adj_angle(ang + (size_t)(k0 + ka) * kAngleStride, (int)threadIdx.x < K, g.cW,
+                                   (double)tile.x0 - g.cW, (double)tile.y0 - g.cW, W, ka);
+  }
+  __syncthreads();
+  // item: 4 slices (l) of one bin, slice octet and angle
+  const float* Sz = S + (size_t)tile.zb * (Wp * 128);
+  for (int i = threadIdx.x; i < NA * NT * NB * 2; i += kAdjThreads) {
+    const int l = i & 1, bin = (i >> 1) % NB, o = (i >> 1) / NB, t = o % NT, a = o / NT;
+    const AdjAngle A = s_ang[a];
+    const float* src = Sz + (size_t)A.row * angw + (size_t)(t * Wp + A.bin0 + bin) * 8 + 4 * l;
+    const SplitTerms s = split_samples(*reinterpret_cast<const float4*>(src),
+                                       *reinterpret_cast<const float4*>(src + (size_t)Wp * 64),
+                                       smax + tile.zb * kAdjZT + 8 * t + 4 * l);
+    uint4* dst = tile4 + ((a >> 1) * (ROWS / 2) + 2 * t * NB + bin) * 4 + (a & 1) * 2 + l;
+    dst[0] = s.first;
+    dst[NB * 4] = s.second;
+  }
+  __syncthreads();
+  const int m = lane & 15, ga = lane >> 4;
+  const int bx = 4 * (wave & 3), by = 8 * (wave >> 2);
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint4*)tile4;
+  const unsigned lp = lds0 + (unsigned)((ga >> 1) * (ROWS * 32) + (m >> 2) * 64 + (ga & 1) * 32 + (m & 3) * 8);
+  float minus1 = -1.0f;
+  asm volatile("" : "+s"(minus1));
+  const size_t WW = (size_t)W * W;
+#pragma unroll 1
+  for (int b = 0; b < 2; ++b) {
+    const int yb = by + 4 * b;
+    const AdjWeights w = adj_weights(s_ang[ga], (float)bx, (float)yb, (float)(bx + (m & 3)),
+                                     (float)(yb + (m >> 2)), minus1);
+    const LdsHalf4 wp = (LdsHalf4)(uintptr_t)(lp + 64u * (unsigned)w.bin);
+#pragma unroll 2
+    for (int t = 0; t < NT; ++t) {
+      const half8 h1 = adj_read8(wp, (2 * t) * NB * 8), h2 = adj_read8(wp, (2 * t + 1) * NB * 8);
+      float4v r = (float4v)(0.f);
+      r = __builtin_amdgcn_mfma_f32_16x16x32_f16(w.w2, h1, r, 0, 0, 0);
+      r = __builtin_amdgcn_mfma_f32_16x16x32_f16(w.wt, h2, r, 0, 0, 0);
+      r = __builtin_amdgcn_mfma_f32_16x16x32_f16(w.w1, h1, r, 0, 0, 0);
+      const int z = tile.zb * kAdjZT + 8 * t + (m >> 1);
+      adj_store(r, smax, z, (m & 1) != 0,
+                gu + (size_t)z * WW + (size_t)(tile.y0 + yb + ga) * W + tile.x0 + bx);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -773,11 +883,15 @@ hipError_t launch_radon_adj(const DevGeom& g, float2* S, float2* gu, const doubl
   if (K < 1 || g.H % kAdjZT != 0 || g.W % 16 != 0) return hipErrorInvalidValue;
   unsigned* Sw = reinterpret_cast<unsigned*>(S);
   const int Wp = sino_row(g.W), nzb = g.H / kAdjZT;
+  const unsigned n = (unsigned)(g.W / 16) * (unsigned)(g.W / 16) * (unsigned)nzb;
+  if (K <= 4) {
+    k_radon_adj_few<<<n, kAdjThreads, 0, st>>>(reinterpret_cast<const float*>(S), gu, g, ang, k0, K, smax);
+    return hipGetLastError();
+  }
   const size_t ns = (size_t)K * nzb * Wp * 16;
   k_split_sino<<<split_sino_blocks(ns), kThreads, 0, st>>>(Sw, smax, ns, Wp, nzb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const unsigned n = (unsigned)(g.W / 16) * (unsigned)(g.W / 16) * (unsigned)nzb;
   // A volume of fewer tiles than CUs (one workgroup each) shares its angles
   // out too, at least 4 groups of them to a share, into volumes in `tmp`.
   // 64^3, 90 angles (16 tiles): 45 -> 27 us in 5 shares; 128^3, 180 angles
