@@ -13,6 +13,7 @@
 //   radon_adj_few the same over up to four angles, without the split pass
 // None is bound by HBM: every voxel is revisited once per angle.
 #include <algorithm>
+#include <type_traits>
 
 #include "holo_internal.hpp"
 
@@ -96,11 +97,14 @@ __global__ __launch_bounds__(kThreads) void k_block_volume(const float2* __restr
 // one column: free of bank conflicts.  Angles that walk along x read the
 // x/y-transposed volume, so both walk directions use the same code.  The
 // host groups angles so that every window fits.
-// HALF (NB = 8, W at most kHalfMaxW): half of a 16-bin block, with windows of
-// its own.  Tap positions are taken from the lowest column of the whole
+// HALF (NB = 8): half of a 16-bin block, with windows of its own.  Tap positions are taken from the lowest column of the whole
 // block's window and its thread's first bin, so every tap and weight, and
-// with them the fields, are the bits that a 16-bin workgroup gives.
-constexpr int kHalfMaxW = 1024;
+// with them the fields, are the bits that a 16-bin workgroup gives.  The taps
+// of a half span 8 columns less than a group may (its angles' bins all run the
+// same way, at least a column each): kFwdSeg - 12, so 26 columns hold them and
+// their margins.
+constexpr int kHalfSeg = 26;
+static_assert(kHalfSeg == kFwdSeg - 6 && kHalfSeg % 2 == 0, "window of a half");
 template <int NB, bool HALF>
 __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restrict__ u,
                                                          const float2* __restrict__ uT,  // z-blocked
@@ -108,19 +112,19 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
                                                          const double* __restrict__ ang,
                                                          const int2* __restrict__ groups,
                                                          int g0, int ngroups, int c0, int c1) {
-  constexpr int ZT = kFwdZT, SEG = kFwdSeg, ZB = kVolZB;
+  constexpr int ZT = kFwdZT, SEG = HALF ? kHalfSeg : kFwdSeg, ZB = kVolZB;
   constexpr int BPT = NB / 4;                       // bins per thread
   constexpr int NBUF = 3;                           // row buffers (loads run 2 rows ahead)
   constexpr int ROWF2 = SEG * ZT;                   // float2 per staged row
-  constexpr int LPW = ROWF2 / (4 * 128);            // LDS-direct loads (16 B per lane) per wave per row
   constexpr int C4 = ZT / 2;                        // float4 per staged column
-  static_assert(ZT == 64 && (NB == 16 || NB == 8) && LPW == 4 && kThreads == 256, "tiling");
+  static_assert(ZT == 64 && (NB == 16 || NB == 8) && SEG <= 32 && kThreads == 256, "tiling");
   static_assert(!HALF || NB == 8, "half of a 16-bin block");
   __shared__ float4 tile4[NBUF * ROWF2 / 2];
-  __shared__ unsigned short s_win[kMaxW];           // 16 (xl + 64) + pairs of columns - 1
-  // HALF: first column of the window minus that of the whole block (0 where
-  // the window was moved)
-  __shared__ unsigned char s_dx[HALF ? kHalfMaxW : 1];
+  // rows' windows: 16 (xl + 64) + pairs of columns - 1.  HALF: xl of the whole
+  // block, from bit 16 the half's first column from there (at most 12), or
+  // kMoved and its own xl where it was moved
+  constexpr int kMoved = 1 << 20;
+  __shared__ typename std::conditional<HALF, unsigned, unsigned short>::type s_win[kMaxW];
   __shared__ int s_first, s_last;                   // rows whose window meets the volume
   const int W = g.W, H = g.H;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -175,14 +179,18 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
       const double f0 = fr + (double)sb * ap[kB], f1 = fr + (double)(sb + NB - 1) * ap[kB];
       mn = fmin(mn, fmin(f0, f1));
       mx = fmax(mx, fmax(f0, f1));
-      if constexpr (HALF)
-        mn16 = fmin(mn16, fmin(fr + (double)(sb & ~15) * ap[kB], fr + (double)(sb | 15) * ap[kB]));
+      // (the whole block's other end bin)
+      if constexpr (HALF) mn16 = fmin(mn16, fr + (double)((sb & 8) != 0 ? sb - 8 : sb + 15) * ap[kB]);
     }
     const int lo = (int)floor(mn) - 1, hi = (int)floor(mx) + 2;   // columns lo .. hi
     const int xl = min(max(lo, -kFwdPad), W + kFwdPad - SEG);
     const int pairs = xl == lo ? min((hi - lo + 2) / 2, SEG / 2) : SEG / 2;
-    s_win[r] = (unsigned short)(16 * (xl + 64) + pairs - 1);
-    if constexpr (HALF) s_dx[r] = (unsigned char)(xl == lo ? lo - ((int)floor(mn16) - 1) : 0);
+    if constexpr (HALF) {
+      const int lo16 = xl == lo ? (int)floor(fmin(mn, mn16)) - 1 : xl;
+      s_win[r] = (unsigned)(16 * (lo16 + 64) + pairs - 1 + (xl == lo ? (lo - lo16) << 16 : kMoved));
+    } else {
+      s_win[r] = (unsigned short)(16 * (xl + 64) + pairs - 1);
+    }
     const unsigned long long in = __ballot(hi >= 0 && lo < W);
     if (in) {
       first = min(first, r - lane + __builtin_ctzll(in));
@@ -215,9 +223,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
   const int wv = __builtin_amdgcn_readfirstlane(wave);
   // loads of row y (its s_win entry: win) into buffer buf; returns how many
   // this wave issued
-  auto xl_of = [](int win) { return ((HALF ? win & 0xffff : win) >> 4) - 64; };
+  auto base_of = [](int win) { return (HALF ? win >> 4 & 0xfff : win >> 4) - 64; };   // of the taps
+  auto dx_of = [](int win) { return HALF ? win >> 16 & 15 : 0; };
   auto issue = [&](int y, int win, int buf) {
-    const int xl = xl_of(win), n = ((win & 15) + 4 - wv) >> 2;
+    const int xl = base_of(win) + dx_of(win), n = ((win & 15) + 4 - wv) >> 2;
     const float2* row = vl + ((ptrdiff_t)y * Wf + xl) * ZB;
     const unsigned dst = lds0 + (unsigned)((buf * (ROWF2 / 2) + wv * 64) * 16);
     auto load = [&](int i) {
@@ -260,12 +269,9 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
 #pragma unroll
     for (int e = 0; e < 4; ++e) { ax[b][e] = ay[b][e] = 0.f; ox[b][e] = oy[b][e] = 0.0; }
 
-  // a row's window, HALF: with s_dx above it
-  auto win_at = [&](int y) {
-    const int r = min(y, W - 1);
-    return HALF ? (int)s_win[r] | (int)s_dx[r] << 16 : (int)s_win[r];
+  auto win_of = [&](int y) {
+    return __builtin_amdgcn_readfirstlane((int)s_win[min(y, W - 1)]);
   };
-  auto win_of = [&](int y) { return __builtin_amdgcn_readfirstlane(win_at(y)); };
   // windows of rows y, y + 1 and y + 2 (read from LDS a row before use)
   int win0 = win_of(y_beg), win1 = win_of(y_beg + 1), win2 = win_of(y_beg + 2);
   int cur = 0, fly = 0;                             // buffer of row y; loads of row y + 1
@@ -280,14 +286,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     fly = y + 2 < y_end ? issue(y + 2, win2, cur == 0 ? 2 : cur - 1) : 0;
-    const int win3 = win_at(y + 3);
+    const int win3 = (int)s_win[min(y + 3, W - 1)];
     if (active) {
       // tap position of the thread's first bin relative to the window, in
       // double precision; the other bins add b B (< 4 sqrt(2))
-      const int dx = HALF ? win0 >> 16 : 0;
-      float rel = (float)(fA + (double)y * D - (double)(xl_of(win0) - dx));
-      rel = fminf(fmaxf(rel, rel_lo), rel_hi);
-      int tb = cur * (ROWF2 / 2) + pz - dx * C4;
+      float rel = (float)(fA + (double)y * D - (double)base_of(win0));
+      // (HALF: only moved windows, whose clamp fits the narrower window)
+      if (!HALF || (win0 & kMoved) != 0) rel = fminf(fmaxf(rel, rel_lo), rel_hi);
+      int tb = cur * (ROWF2 / 2) - dx_of(win0) * C4 + pz;
       asm volatile("" : "+v"(tb));                     // one base register per row
       const float4* tr = tile4 + tb;
       // software pipeline: the taps of bin b + 1 are requested before bin b
@@ -853,7 +859,7 @@ hipError_t launch_radon_fwd(const DevGeom& g, const float2* ub, const float2* uT
   // us, but 704 (256 px) 256 -> 325.
   if (nb == 8)
     k_radon_fwd<8, false><<<n8, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0, c1);
-  else if (nb == kFwdNB && by_size && n16 < 512 && g.W <= kHalfMaxW)
+  else if (nb == kFwdNB && by_size && n16 < 512)
     k_radon_fwd<8, true><<<n8, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups, c0, c1);
   else if (nb == kFwdNB)
     k_radon_fwd<kFwdNB, false><<<n16, kThreads, 0, st>>>(ub, uTb, psi, g, ang, groups, g0, ngroups,

@@ -5,25 +5,26 @@ runs."""
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import holo_oracle as O
-from tests.problems import assert_close, c128, gpu_plan, make_problem
+from paper_2407_20304_amd import synth
+from tests.problems import Problem, assert_close, c128, gpu_plan
 
 pytestmark = pytest.mark.gpu
 
 
-def _problem(W, n):
-    p = make_problem(64, W, 2, config=63, mag_rel=(1.0,))
+def _problem(W, angles):
+    """Every voxel carries weight; a number of angles over the half-turn, or
+    the angles.  (No data: the fields alone are looked at.)"""
+    theta = np.arange(angles) * (np.pi / angles) if np.ndim(angles) == 0 else angles
     rng = np.random.default_rng(4)
-    p.u = (rng.uniform(0, 2e-6, p.u.shape) * (1 + 0.01j)).astype(np.complex64)
-    g = p.geom
-    p.geom = O.Geometry(H=64, W=W, theta=np.arange(n) * (np.pi / n) if np.ndim(n) == 0 else n, mag_rel=g.mag_rel, m0=g.m0,
-                        fresnel0=g.fresnel0, kappa=g.kappa)
-    return p
+    u = (rng.uniform(0, 2e-6, (64, W, W)) * (1 + 0.01j)).astype(np.complex64)
+    geom = O.Geometry(H=64, W=W, theta=theta, mag_rel=(1.0,), m0=synth.M0, fresnel0=synth.FRESNEL0, kappa=synth.KAPPA)
+    return Problem(geom, u, synth.probe(64, W, 3), None, None, 0)
 
 
 def _fields(plan, p, *k):
-    import torch
     dev = torch.device("cuda:0")
     return plan.holo_fwd(torch.from_numpy(p.u).to(dev), torch.from_numpy(p.q).to(dev), *k).cpu().numpy()
 
@@ -34,8 +35,9 @@ EDGES = np.array([0.0, 1e-9, np.pi / 4 - 1e-6, np.pi / 4, np.pi / 4 + 1e-6, np.p
 
 # 64 px: halves in every launch; 512: in short ones; edges: axes, the walk
 # switch, windows outside the volume at either end
-@pytest.mark.parametrize("W,n", [(64, 90), (512, 70), (192, EDGES), (1024, EDGES[:7])],
-                         ids=["64", "512", "192-edges", "1024-edges"])
+@pytest.mark.parametrize("W,n", [(64, 90), (512, 70), (192, EDGES), (1024, EDGES[:7]),
+                                 (2048, EDGES[2:5])],
+                         ids=["64", "512", "192-edges", "1024-edges", "2048-edges"])
 def test_the_same_bits_in_every_chunk_and_range(W, n):
     p = _problem(W, n)
     n = len(p.geom.theta)
@@ -46,7 +48,7 @@ def test_the_same_bits_in_every_chunk_and_range(W, n):
     plan = gpu_plan(p)
     assert (_fields(plan, p) == v).all()
     groups = plan.ray_groups()
-    k0, k1 = groups[-4][0], groups[-1][0]
+    k0, k1 = groups[max(0, len(groups) - 4)][0], groups[-1][0]
     assert (_fields(plan, p, k0, k1) == v[k0:k1]).all()
     for chunk in (4, 17, 31):
         plan.set_chunk(chunk)
