@@ -414,7 +414,6 @@ holo_status b2_launch(holo2d_plan* P, B2Run run, const char* tb, char* w, const 
     if (run != kB2Fwd) B2_HIP(launch_fill_zero((float2*)A.Fpart, (size_t)P->n_slots, st));
     if (grad && g_q) B2_HIP(launch_fill_zero((float2*)g_q, (size_t)P->total, st));
   } else {
-    A.mode = kB2RowsProbe;
     const ItemList& rp = want_ref ? P->rows_probe : P->rows_probe_noref;
     B2_HIP(launch_b2_probe_rows(A, items(rp), (int)rp.items.size(), st));
     A.mode = kB2ColsProbe;

@@ -28,9 +28,9 @@ struct B2Item {
   int inst, job, line0, slot;
 };
 
-// Passes of the batched gradient (one launch each):
-//   kB2RowsProbe  rows of D_{rho_probe_j} q (jobs < nd) and of D_1 q (job nd)
-//                 from one transform of each row of q
+// Passes of the batched gradient (one launch each), after the probe rows
+// (launch_b2_probe_rows: rows of D_{rho_probe_j} q, jobs < nd, and of D_1 q,
+// job nd, from one transform of each row of q):
 //   kB2ColsProbe  their columns; job nd: reference residual and cost, then
 //                 (want_gq) the columns of D_{-1} on it
 //   kB2RowsA      pass A rows;  kB2ColsB  pass B columns
@@ -41,7 +41,7 @@ struct B2Item {
 //                 G_j summed in the frequency domain, one inverse transform,
 //                 plus the reference term -> g_q
 enum B2Mode {
-  kB2RowsProbe = 0, kB2RowsA, kB2RowsC, kB2RowsCGq,
+  kB2RowsA, kB2RowsC, kB2RowsCGq,
   kB2ColsProbe, kB2ColsB, kB2ColsGqSum
 };
 

@@ -123,8 +123,9 @@ bool fft_size_supported(int n);
 bool col_tile_supported(int H, int tc);
 // Ray-sum tiling (see the kernels): forward angle-group size, slices and
 // bins per workgroup, staged rows per block and staged columns per row;
-// transpose slices and threads per workgroup, bins per staged segment and power of two of the footprint weights; slice blocking of the
-// forward's volume copies.
+// transpose slices and threads per workgroup, bins per staged segment and
+// power of two of the footprint weights; slice blocking of the forward's
+// volume copies.
 constexpr int kFwdNA = 4, kFwdZT = 64, kFwdNB = 16, kFwdYB = 2, kFwdSeg = 32;
 constexpr int kAdjZT = 64, kAdjBins = 26, kAdjThreads = 512, kAdjWScale = 14;
 constexpr int kAdjWin = 64;   // angles per transpose set-up window

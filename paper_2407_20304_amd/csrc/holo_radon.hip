@@ -570,9 +570,10 @@ __device__ __forceinline__ half8 adj_read8(LdsHalf4 wp, int o) {
 // operand comes from transposing LDS reads: 16 lanes read 4 bins x 16 columns
 // stored with the columns fastest, and each lane receives the 4 bins of one
 // column (two-address reads of single words took 4.4 clocks of LDS per 512
-// bytes, these 2.1 in the counters, and any first bin is aligned).  In LDS the 32 bytes (16 columns) of one bin alternate between two
-// angles: the 4 bins of two angles that one pass of a read serves lie on
-// different banks wherever their windows start.  Partial sums of 32 angles
+// bytes, these 2.1 in the counters, and any first bin is aligned).  In LDS the
+// 32 bytes (16 columns) of one bin alternate between two angles: the 4 bins of
+// two angles that one pass of a read serves lie on different banks wherever
+// their windows start.  Partial sums of 32 angles
 // are added into outer sums.
 __global__ __launch_bounds__(kAdjThreads, 2) void k_radon_adj(const unsigned* __restrict__ S,
                                                               float2* __restrict__ gu, DevGeom g,
