@@ -34,12 +34,12 @@ FLOP_PER_LERP = 8               # 2 taps x (re, im) x fused multiply-add
 # KERNEL_SOURCES) and the workload they were taken on; after any change to
 # those sources, or on another workload, the field reports null.
 TRAFFIC = {
-    "k_radon_fwd": {"workload": "vol1024_a1800", "fetch_kib": 25575894.70, "write_kib": 508471.47,
+    "k_radon_fwd": {"workload": "vol1024_a1800", "fetch_kib": 25463749.37, "write_kib": 508471.31,
                     "fetch_scale": 2.0, "write_scale": 1.0,
-                    "sources_sha256": "d81f9b1a45e4b94005261f0e59d9dde3da6eda40905c42a21801d7d446b52da5"},
-    "k_radon_adj": {"workload": "vol1024_a1800", "fetch_kib": 116201090.56, "write_kib": 8394915.97,
+                    "sources_sha256": "e53791487bd23404ec831dae397e2a941e2434cfb4d133c783fa1fad5c4f61d6"},
+    "k_radon_adj": {"workload": "vol1024_a1800", "fetch_kib": 116201087.62, "write_kib": 8391888.12,
                     "fetch_scale": 2.0, "write_scale": 1.0,
-                    "sources_sha256": "d81f9b1a45e4b94005261f0e59d9dde3da6eda40905c42a21801d7d446b52da5"},
+                    "sources_sha256": "e53791487bd23404ec831dae397e2a941e2434cfb4d133c783fa1fad5c4f61d6"},
 }
 
 

@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_radon_fwd(const float2* __restr
 // leaves of a weight of 1 (positions of up to 21 bins, held to 2^-20).  On
 // the vector units the same sums took 8.6 instructions and 8 bytes of LDS
 // reads per voxel, slice and angle against 4 bytes and 24 products of
-// 16 x 16 x 32 per 16 x 64 x 4 of them here: 345 -> 201 ms at 1024^3 x 1800
+// 16 x 16 x 32 per 16 x 64 x 4 of them here: 345 -> 190 ms at 1024^3 x 1800
 // angles, conversion included.  Every slice of h is scaled by a power of two
 // (its largest finite value to 2^14 .. 2^15) and the weights by
 // 2^kAdjWScale; h2 is stored times 2^kAdjTail and multiplied by w1
